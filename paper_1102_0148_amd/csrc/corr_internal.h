@@ -12,6 +12,11 @@ constexpr int kFP32 = 0;
 constexpr int kFP16 = 1;
 constexpr int kINT8 = 2;
 constexpr int kINT16 = 3;
+// X-stage only: the float records of the library's own F-stage, multiplied as
+// f16 halves (see xstage_dev.h).  Their components are at most 16384, so the
+// halves cannot overflow; records a caller supplies have no such bound and are
+// multiplied as kFP32.
+constexpr int kFP32H = 4;
 // the requantised forms, which take per-(antenna, channel) scales
 __host__ __device__ constexpr bool is_quant(int prec) { return prec == kINT8 || prec == kINT16; }
 // int16 values: |q| <= 32512 = 255 * 127 + 127, each stored as two int8
@@ -40,9 +45,13 @@ constexpr int kF16SplitSpectra = 16384;
 // form a k-block of the X-stage.
 constexpr int kRecordBytes = 16;
 __host__ __device__ constexpr int record_times(int prec) {
-    return prec == kFP32 ? 2 : (prec == kINT8 ? 8 : 4);
+    return prec == kFP32 || prec == kFP32H ? 2 : (prec == kINT8 ? 8 : 4);
 }
 __host__ __device__ constexpr int kblock_times(int prec) { return 4 * record_times(prec); }
+// Records the F-stage pads a chunk to: whole X-stage steps, which are one
+// k-block, or two for int16 and for float records taken as halves (one 16-byte
+// operand then holds two records' digits or halves).
+__host__ __device__ constexpr int step_records(int prec) { return prec == kFP32 || prec == kINT16 ? 8 : 4; }
 
 // Records are grouped in time blocks of kTQB consecutive records:
 // [time block][channel][kTQB records][antenna_pad].  The F-stage's writes of

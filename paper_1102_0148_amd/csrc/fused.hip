@@ -104,7 +104,7 @@ __device__ __forceinline__ void fx_f_role(const FxArgs &a, float2 *zbuf, uint32_
         fa.in = a.f.in + (int64_t)c * a.chunk * frame;
         fa.s_base = c * a.chunk;
         fa.S = Sc;
-        const int ntq_used = ((Sc + tg - 1) / tg + 3) / 4 * 4;
+        const int ntq_used = ((Sc + tg - 1) / tg + step_records(PREC) - 1) / step_records(PREC) * step_records(PREC);
         fa.ntiles = ntq_used * fa.ngroups;
         const int t8 = (fa.ntiles + 7) / 8;
         const int lo = x * t8, hi = min(lo + t8, fa.ntiles);
@@ -120,7 +120,9 @@ __device__ __forceinline__ void fx_x_role(const FxArgs &a, int xrank, float *tb)
     const int unit = xrank * 4 + w;
     const bool active = unit < a.x.K * a.x.nsplit;
     const int f = unit % a.x.K, sp = unit / a.x.K;
-    XRegion<PREC, RB, true> acc;
+    constexpr int XP = PREC == kFP32 ? kFP32H : PREC;
+    typedef XRegion<XP, RB, true> Region;
+    Region acc;
     acc.zero();
     int epoch = 0;
     for (int c = 0; c < a.nchunks; ++c) {
@@ -128,11 +130,11 @@ __device__ __forceinline__ void fx_x_role(const FxArgs &a, int xrank, float *tb)
         if (threadIdx.x == 0) fx_wait(cc + kFxDone, 8u, a.err);
         __syncthreads();
         const int Sc = min(a.chunk, a.S - c * a.chunk);
-        const int nkb = ((Sc + tg - 1) / tg + 3) / 4;
+        const int nst = ((Sc + tg - 1) / tg + 4 * Region::KB - 1) / (4 * Region::KB);
         if (active) {
-            const int kb0 = (int)((int64_t)sp * nkb / a.x.nsplit);
-            const int kb1 = (int)((int64_t)(sp + 1) * nkb / a.x.nsplit);
-            acc.template run<kFxXBuf>(a.f.spec + (int64_t)(c % a.ring) * a.slot_recs, a.x.K, a.x.a_pad, f, 0, 0,
+            const int kb0 = (int)((int64_t)sp * nst / a.x.nsplit);
+            const int kb1 = (int)((int64_t)(sp + 1) * nst / a.x.nsplit);
+            acc.template run<(Region::KB == 2 ? 2 : kFxXBuf)>(a.f.spec + (int64_t)(c % a.ring) * a.slot_recs, a.x.K, a.x.a_pad, f, 0, 0,
                                       kb0, kb1);
         }
         // every load of the chunk has returned before the slot can be reused

@@ -421,7 +421,17 @@ int timers_collect(corr_ctx *h) {
     return CORR_OK;
 }
 
-int launch_x_and_dump(corr_ctx *h, const uint4 *spec, int ntq, int nkb, hipStream_t st) {
+// `own`: the records are the F-stage's (padded to whole steps, components at
+// most 16384); false: a caller's.
+int launch_x_and_dump(corr_ctx *h, const uint4 *spec, int ntq, int nkb, bool own, hipStream_t st) {
+    // Float records as halves but where that gains nothing: one block of antennas
+    // streams its records as fast through the f32 products (N = 16, K = 512, 16384
+    // spectra: 176 us, 168 as halves), and in partials of a few spectra, where the
+    // launch is latency, the f32 products round no more often than the halves
+    // (against float64, N = 24, 64 spectra in 16 splits: 9.3e-8, halves 9.6e-8;
+    // 37 spectra a split, N = 44: 9.7e-8, halves 8.9e-8).
+    const bool halves = own && h->nblk > 1 && nkb * 8 >= h->tiles.x_splits * 32;
+    const int xprec = h->prec == kFP32 && halves ? kFP32H : h->prec;
     XArgs xa{};
     xa.spec = spec;
     xa.partial = h->partial;
@@ -440,28 +450,28 @@ int launch_x_and_dump(corr_ctx *h, const uint4 *spec, int ntq, int nkb, hipStrea
         // 16 blocks: one workgroup per channel stages them all in LDS once per
         // k-block (the three region groups would fetch every block twice;
         // fp32's own 4x4 off-diagonal regions run one wave per SIMD)
-        HIP_TRY(launch_xchan(h->prec, xa, st), "X-stage launch");
+        HIP_TRY(launch_xchan(xprec, xa, st), "X-stage launch");
     } else if (h->n_xgroups && half_or_byte) {
         // groups of regions that share blocks stage them in LDS once per
         // k-block, with the loads two k-blocks ahead
         xa.groups = h->xgroups;
         xa.ngroups = h->n_xgroups;
-        HIP_TRY(launch_xgroups(h->prec, xa, st), "X-stage launch");
+        HIP_TRY(launch_xgroups(xprec, xa, st), "X-stage launch");
     } else if (h->n_off && half_or_byte) {
         // one launch over every region of a channel (diagonal ones first), so
         // the regions that share records read them from HBM once, through one
         // L2: the int8 and fp16 forms are bound by that traffic
         xa.nregions = h->n_diag + h->n_off;
-        HIP_TRY(launch_xstage(h->prec, h->rb, 2, xa, st), "X-stage launch");
+        HIP_TRY(launch_xstage(xprec, h->rb, 2, xa, st), "X-stage launch");
     } else {
         // fp32 is bound by MFMA rate, and its diagonal regions keep more waves
         // per SIMD in a launch of their own
         xa.nregions = h->n_diag;
-        HIP_TRY(launch_xstage(h->prec, h->rb, 1, xa, st), "X-stage launch");
+        HIP_TRY(launch_xstage(xprec, h->rb, 1, xa, st), "X-stage launch");
         if (h->n_off) {
             xa.regions = h->regions + h->n_diag;
             xa.nregions = h->n_off;
-            HIP_TRY(launch_xstage(h->prec, h->rb, 0, xa, st), "X-stage launch");
+            HIP_TRY(launch_xstage(xprec, h->rb, 0, xa, st), "X-stage launch");
         }
     }
     timer_end(h, st);
@@ -563,8 +573,7 @@ int process_one(corr_ctx *h, const uint8_t *in, hipStream_t st) {
     }
     for (int c0 = 0; c0 < h->S; c0 += chunk) {
         const int Sc = std::min(chunk, h->S - c0);
-        // whole k-blocks; int16 steps take two k-blocks
-        const int ntq_used = round_up((Sc + h->TG - 1) / h->TG, h->prec == kINT16 ? 8 : 4);
+        const int ntq_used = round_up((Sc + h->TG - 1) / h->TG, step_records(h->prec));
         FArgs fa{};
         // through a slot, the kernel adds the chunk's offset (s_base) itself
         fa.in = h->in_slot ? nullptr : in + (int64_t)c0 * frame;
@@ -586,7 +595,7 @@ int process_one(corr_ctx *h, const uint8_t *in, hipStream_t st) {
         HIP_TRY(launch_fstage(h->K, h->prec, ga, 0, fa, 0, st), "F-stage launch");
         timer_end(h, st);
         h->launches_f++;
-        int rc = launch_x_and_dump(h, h->spec, h->ntq_buf, ntq_used / 4, st);
+        int rc = launch_x_and_dump(h, h->spec, h->ntq_buf, ntq_used / 4, true, st);
         if (rc) return rc;
         h->last_chunk = Sc;
         h->dbg_spec = h->spec;
@@ -944,7 +953,7 @@ int corr_process_spectra(corr_handle hh, const void *spectra, int n_spectra, voi
         const int n = (int)std::min<int64_t>(range, n_spectra - s0);
         const int ntq = round_up((n + h->TG - 1) / h->TG, h->prec == kINT16 ? 8 : 4);
         const uint4 *base = (const uint4 *)spectra + (s0 / tb_spectra) * h->K * kTQB * h->a_pad;
-        rc = launch_x_and_dump(h, base, ntq, ntq / 4, st);
+        rc = launch_x_and_dump(h, base, ntq, ntq / 4, false, st);
         if (rc) return rc;
     }
     h->accumulated += n_spectra;
@@ -1181,7 +1190,7 @@ int batch_build(corr_ctx *b) {
         const int c0 = j * kBatchCounters;
         const int ga = h->tiles.f_group;
         const int ngroups = (h->N + ga - 1) / ga;
-        const int ntq_used = round_up((h->S + h->TG - 1) / h->TG, 4);
+        const int ntq_used = round_up((h->S + h->TG - 1) / h->TG, step_records(h->prec));
         BJob &d = bj[j];
         std::memset(&d, 0, sizeof d);
         d.f.spec = h->spec;

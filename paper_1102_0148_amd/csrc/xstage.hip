@@ -16,7 +16,7 @@ constexpr int kOffDiag = 0, kDiag = 1, kBoth = 2;
 // more than 256 registers and keep the default.
 template <int PREC, int RB, int KIND>
 constexpr int x_min_blocks() {
-    return (PREC == kFP32 && ((RB >= 4 && KIND != kDiag) || RB >= 6)) ? 1 : 2;
+    return ((PREC == kFP32 || PREC == kFP32H) && ((RB >= 4 && KIND != kDiag) || RB >= (PREC == kFP32 ? 6 : 5))) ? 1 : 2;
 }
 
 template <int PREC, int RB, int KIND>
@@ -172,11 +172,26 @@ __global__ __launch_bounds__(kXChanWaves * 64, 1) void xchan_kernel(XArgs a) {
     }
 }
 
+// Float records as halves: two raw buffers and two of halves (4 x 32 KB), each an
+// array of its own as above.
+__global__ __launch_bounds__(kXChanWaves * 64, 1) void xchan_halves_kernel(XArgs a) {
+    __shared__ __attribute__((aligned(16))) uint4 raw0[kXHalvesRaw];
+    __shared__ __attribute__((aligned(16))) uint4 raw1[kXHalvesRaw];
+    __shared__ __attribute__((aligned(16))) uint4 hv0[kXHalvesBuf];
+    __shared__ __attribute__((aligned(16))) uint4 hv1[kXHalvesBuf];
+    __shared__ float tb[4 * 16 * 17];
+    const int lb = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    x_chan_halves(a, lb, raw0, raw1, hv0, hv1, tb);
+}
+
 template <int PREC>
 hipError_t launch_chan(const XArgs &a, hipStream_t st) {
     const int64_t units = (int64_t)a.K * a.nsplit;
     const int grid = (int)(8 * ((units + 7) / 8));  // a multiple of 8; units past the end exit
-    hipLaunchKernelGGL((xchan_kernel<PREC>), dim3(grid), dim3(kXChanWaves * 64), 0, st, a);
+    if constexpr (PREC == kFP32H)
+        hipLaunchKernelGGL(xchan_halves_kernel, dim3(grid), dim3(kXChanWaves * 64), 0, st, a);
+    else
+        hipLaunchKernelGGL((xchan_kernel<PREC>), dim3(grid), dim3(kXChanWaves * 64), 0, st, a);
     return hipGetLastError();
 }
 
@@ -185,6 +200,7 @@ hipError_t launch_chan(const XArgs &a, hipStream_t st) {
 hipError_t launch_xchan(int prec, const XArgs &a, hipStream_t st) {
     switch (prec) {
         case kFP32: return launch_chan<kFP32>(a, st);
+        case kFP32H: return launch_chan<kFP32H>(a, st);
         case kFP16: return launch_chan<kFP16>(a, st);
         case kINT8: return launch_chan<kINT8>(a, st);
     }
@@ -240,6 +256,7 @@ hipError_t launch_xstage(int prec, int rb, int kind, const XArgs &a, hipStream_t
     if (prec == kINT16) return launch_xstage16(rb, kind, a, st);
     switch (prec) {
         case kFP32: return launch_p<kFP32>(rb, kind, a, st);
+        case kFP32H: return launch_p<kFP32H>(rb, kind, a, st);
         case kFP16: return launch_p<kFP16>(rb, kind, a, st);
         case kINT8: return launch_p<kINT8>(rb, kind, a, st);
     }

@@ -12,8 +12,11 @@
 // since sum_k Q_a[k] P_b[k] = sum_t (im_a re_b - re_a im_b).  One 16-byte
 // record per lane is exactly one MFMA operand for the fp16 (16x16x32) and
 // int8 (16x16x64) forms, and four consecutive operands for fp32 (16x16x4).
-// The fp32 form, which is bound by MFMA rate rather than by memory, issues
-// fewer products: off the diagonal it uses three real products instead of
+// Float records of the library's own F-stage are multiplied as f16 halves (below,
+// kFP32H), two records to an operand.  Float records a caller supplies, and
+// launches the halves gain nothing in, take the f32 instructions, whose form is
+// bound by MFMA rate rather than by memory and issues fewer products: off the
+// diagonal it uses three real products instead of
 // four (P1 = Xr Xr^T, P2 = Xi Xi^T, P3 = (Xr+Xi)(Xr-Xi)^T give Re = P1 + P2
 // and Im = P3 - P1 + P2), and on a diagonal block Re = P1 + P2 in one
 // accumulator and Im = M - M^T with M = Xi Xr^T (so autos are exactly real).
@@ -28,6 +31,8 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
 template <int PREC> struct AccT { typedef f32x4 type; };
 template <> struct AccT<kINT8> { typedef i32x4 type; };
@@ -56,7 +61,7 @@ __device__ __forceinline__ void mma(typename AccT<PREC>::type &acc, uint4 a, uin
         acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
-    } else if constexpr (PREC == kFP16) {
+    } else if constexpr (PREC == kFP16 || PREC == kFP32H) {
         f16x8 av, bv;
         __builtin_memcpy(&av, &a, 16);
         __builtin_memcpy(&bv, &b, 16);
@@ -83,6 +88,115 @@ __device__ __forceinline__ f32x4 mf32(float a, float b, f32x4 acc) {
 }
 
 
+// Float records as f16 halves.  x = hi + lo with hi = x rounded to f16 (ties to
+// even) and lo = x - hi, exact in the f32 arithmetic of the mixed-precision fma,
+// rounded to f16: |x - hi - lo| <= 2^-23 |x| (and 2^-25 below 2^-3).  A product
+// of two values is summed from hi hi, lo hi and hi lo, each exact in the f32
+// accumulator; the lo lo term dropped is below 2^-22 of the product, and of
+// random sign but in the autocorrelations, which it leaves 2^-25 short.  Three
+// f16 products at 16 times the rate of the f32 matrix instructions, and the
+// four-product form, which has none of the three-product form's cancellation:
+// against float64 the sums are nearer than those of the f32 products (relative
+// 2-norm, f32 products and halves: N = 44, K = 256, 65536 spectra 1.65e-7 and
+// 1.0e-7; N = 256, K = 512, 2048 spectra 9.1e-7 and 4.3e-7).  X-stage times, same
+// box: N = 44, 65536 spectra 1.29 -> 1.18 ms (6.4 GB of records at 5.4 TB/s: now
+// bound by reading them); N = 64, K = 512, 16384 spectra 1.07 -> 0.81 ms; N = 160,
+// K = 256, 8192 spectra 2.06 -> 1.50 ms.
+//
+// The halves of two records (four spectra of an antenna) fill one operand, in
+// the f16 record's layout [re x4 | im x4].
+struct Halves {
+    uint4 h, l;
+};
+__device__ __forceinline__ Halves split_records(uint4 r0, uint4 r1, float m1) {
+    const uint32_t x[4][2] = {{r0.x, r0.y}, {r1.x, r1.y}, {r0.z, r0.w}, {r1.z, r1.w}};
+    uint32_t h[4];
+    f16x8 l;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const float a = __uint_as_float(x[w][0]), b = __uint_as_float(x[w][1]);
+        h[w] = __builtin_bit_cast(uint32_t, f16x2{(_Float16)a, (_Float16)b});
+        // one packed conversion: seen through, the halves would be converted
+        // again one by one for the fmas below
+        asm("" : "+v"(h[w]));
+        const f16x2 hv = __builtin_bit_cast(f16x2, h[w]);
+        _Float16 l0 = (_Float16)__builtin_fmaf((float)hv[0], m1, a), l1 = (_Float16)__builtin_fmaf((float)hv[1], m1, b);
+        l[2 * w] = l0;
+        l[2 * w + 1] = l1;
+    }
+    return {make_uint4(h[0], h[1], h[2], h[3]), __builtin_bit_cast(uint4, l)};
+}
+// -1, opaque to the optimizer: a known -1 turns the fma into a subtraction,
+// which has no mixed-precision form
+__device__ __forceinline__ float opaque_m1() {
+    float m1 = -1.0f;
+    asm volatile("" : "+v"(m1));
+    return m1;
+}
+
+// A record from LDS in one 16-byte read (as a struct it becomes two 8-byte
+// ones, whose short offsets cost an address register per block).
+__device__ __forceinline__ uint4 lds_record(const uint4 *p) {
+    const i32x4 v = *reinterpret_cast<const i32x4 *>(p);
+    return make_uint4((uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]);
+}
+
+// [-im | re] of the halves [re | im].
+__device__ __forceinline__ uint4 col_form(uint4 v) {
+    return make_uint4(v.z ^ 0x80008000u, v.w ^ 0x80008000u, v.x, v.y);
+}
+
+// Eight f16 values times 1/2.
+__device__ __forceinline__ uint4 half_of(uint4 v) {
+    f16x8 x = __builtin_bit_cast(f16x8, v);
+    x *= (_Float16)0.5f;
+    return __builtin_bit_cast(uint4, x);
+}
+
+// One step of float records as halves for the pairs of RB row blocks and RBJ
+// column blocks (the row blocks on the diagonal): row(I) and col(J) return the
+// halves of a block's two records.  Im V_IJ =
+// sum P_I C_J^T with C = [-im | re], so that only the column at hand has a
+// second form in registers.  Column by column, the three products of a column's
+// pairs in turn, so that a product waits for no other one.
+//
+// The autocorrelations' sums grow steadily and carry most of the error, a
+// rounding of the whole sum at every product added.  So a diagonal block's Re
+// keeps its small products apart: accR sums hi hi^T alone and acc3 hi lo^T, and
+// Re = accR + acc3 + acc3^T at the end (one product less, too).
+// SERIAL keeps one column's operands at a time in registers.
+template <int RB, bool DIAG, int RBJ, bool SERIAL, typename Row, typename Col>
+__device__ __forceinline__ void add_halves(Row &&row, Col &&col, f32x4 (&accR)[RB][RBJ], f32x4 (&accI)[RB][RBJ],
+                                           f32x4 (&acc3)[RB][RBJ]) {
+    Halves p[RB];
+#pragma unroll
+    for (int I = 0; I < RB; ++I) p[I] = row(I);
+#pragma unroll
+    for (int J = 0; J < RBJ; ++J) {
+        Halves b;
+        if constexpr (DIAG) b = p[J];
+        else b = col(J);
+        const uint4 ch = col_form(b.h), cl = col_form(b.l);
+#pragma unroll
+        for (int I = 0; I < (DIAG ? J + 1 : RB); ++I) {
+            if (DIAG && I == J) mma<kFP32H>(acc3[I][J], half_of(p[I].l), b.l);
+            else mma<kFP32H>(accR[I][J], p[I].l, b.h);
+            mma<kFP32H>(accI[I][J], p[I].l, ch);
+        }
+#pragma unroll
+        for (int I = 0; I < (DIAG ? J + 1 : RB); ++I) {
+            mma<kFP32H>(DIAG && I == J ? acc3[I][J] : accR[I][J], p[I].h, b.l);
+            mma<kFP32H>(accI[I][J], p[I].h, cl);
+        }
+#pragma unroll
+        for (int I = 0; I < (DIAG ? J + 1 : RB); ++I) {
+            mma<kFP32H>(accR[I][J], p[I].h, b.h);
+            mma<kFP32H>(accI[I][J], p[I].h, ch);
+        }
+        if constexpr (SERIAL) __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 // The accumulators of one wavefront's region: RB x RBJ pairs of 16-antenna
 // blocks (DIAG: the upper triangle of a square diagonal region) of one
 // channel, both
@@ -95,6 +209,7 @@ struct XRegion {
     static_assert(!DIAG || RBJ == RB, "a diagonal region is square");
     typedef typename AccT<PREC>::type acc_t;
     static constexpr bool F3M = PREC == kFP32;  // three-product form
+    static constexpr int KB = PREC == kFP32H ? 2 : 1;  // k-blocks per step
     // Q form: accR = Re, accI = Im.  fp32: diagonal pair accR = Re, accI = M;
     // off-diagonal pair accR = P1, accI = P2, acc3 = P3.
     acc_t accR[RB][RBJ], accI[RB][RBJ], acc3[RB][RBJ];
@@ -110,7 +225,7 @@ struct XRegion {
             }
     }
 
-    // k-blocks [kb0, kb1) of channel f, row blocks I0.., column blocks J0..
+    // steps [kb0, kb1) of KB k-blocks each of channel f, row blocks I0.., column blocks J0..
     // NBUF register sets rotate: the records of the next NBUF - 1 k-blocks are
     // in flight while one is multiplied (2 where many waves share a SIMD and
     // hide each other's latency; more for a wave that runs alone).
@@ -123,23 +238,42 @@ struct XRegion {
         const uint4 *base = spec + (int64_t)f * kTQB * a_pad + (lane >> 4) * a_pad + (lane & 15);
         const int64_t bstride = (int64_t)K * kTQB * a_pad;
 
-        // two register sets alternate: the records of the next k-block are in
-        // flight while the current one is multiplied
-        auto load = [&](int kb, uint4 *r, uint4 *c) {
-            const uint4 *rec = base + (kb >> 2) * bstride + (kb & 3) * 4 * a_pad;
+        // two register sets alternate: the records of the next step are in
+        // flight while the current one's are multiplied (below, k-block stands
+        // for a step: kb0, kb1 and kb count steps of KB k-blocks)
+        const float m1 = opaque_m1();
+        auto load = [&](int kb, uint4 (&r)[RB][KB], uint4 (&c)[RBJ][KB]) {
+            const uint4 *rec = base + (kb >> (KB == 2 ? 1 : 2)) * bstride + (kb & (KB == 2 ? 1 : 3)) * 4 * KB * a_pad;
 #pragma unroll
-            for (int I = 0; I < RB; ++I) r[I] = rec[(I0 + I) * 16];
-            if constexpr (!DIAG) {
+            for (int q = 0; q < KB; ++q) {
 #pragma unroll
-                for (int J = 0; J < RBJ; ++J) c[J] = rec[(J0 + J) * 16];
+                for (int I = 0; I < RB; ++I) r[I][q] = rec[q * 4 * a_pad + (I0 + I) * 16];
+                if constexpr (!DIAG) {
+#pragma unroll
+                    for (int J = 0; J < RBJ; ++J) c[J][q] = rec[q * 4 * a_pad + (J0 + J) * 16];
+                }
             }
         };
-        auto compute = [&](const uint4 *pr, const uint4 *pc) { this->add(pr, pc); };
+        auto compute = [&](const uint4 (&pr)[RB][KB], const uint4 (&pc)[RBJ][KB]) {
+            if constexpr (KB == 2) {
+                add_halves<RB, DIAG, RBJ, false>([&](int I) { return split_records(pr[I][0], pr[I][1], m1); },
+                                          [&](int J) { return split_records(pc[J][0], pc[J][1], m1); }, accR, accI, acc3);
+            } else {
+                uint4 r1[RB], c1[RBJ];
+#pragma unroll
+                for (int I = 0; I < RB; ++I) r1[I] = pr[I][0];
+                if constexpr (!DIAG) {
+#pragma unroll
+                    for (int J = 0; J < RBJ; ++J) c1[J] = pc[J][0];
+                }
+                this->add(r1, c1);
+            }
+        };
         // set i holds k-block kb + i at the top of a round; in step i of a round
         // set (i + NBUF - 1) mod NBUF, just freed, is loaded with k-block
         // kb + i + NBUF - 1 (the last one again past the end) and set i is
         // multiplied
-        uint4 r[NBUF][RB], c[NBUF][RBJ];
+        uint4 r[NBUF][RB][KB], c[NBUF][RBJ][KB];
 #pragma unroll
         for (int i = 0; i < NBUF - 1; ++i)
             if (kb0 + i < kb1) load(kb0 + i, r[i], c[i]);
@@ -216,8 +350,21 @@ struct XRegion {
             }
     }
 
+    // The transpose of a 16x16 accumulator block, through tb.
+    __device__ __forceinline__ static f32x4 transposed(const f32x4 &m, float *tb) {
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) tb[(4 * (lane >> 4) + v) * 17 + (lane & 15)] = m[v];
+        wave_lds_sync();
+        f32x4 mt;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) mt[v] = tb[(lane & 15) * 17 + 4 * (lane >> 4) + v];
+        wave_lds_sync();
+        return mt;
+    }
+
     // Write the region into partial row obase ([baseline] of one split and
-    // channel); tb is this wave's 16 x 17 floats of LDS (fp32 form only).
+    // channel); tb is this wave's 16 x 17 floats of LDS (fp32 forms only).
     // The fp32 accumulators are turned into (Re, Im) in place.
     __device__ __forceinline__ void store(void *partial, int64_t obase, int N, int I0, int J0, float *tb) {
         const int lane = threadIdx.x & 63;
@@ -230,20 +377,18 @@ struct XRegion {
                 for (int J = 0; J < RBJ; ++J) {
                     if (DIAG && J < I) continue;
                     if (DIAG && I == J) {
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) tb[(4 * (lane >> 4) + v) * 17 + (lane & 15)] = accI[I][J][v];
-                        wave_lds_sync();
-                        f32x4 mt;
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) mt[v] = tb[(lane & 15) * 17 + 4 * (lane >> 4) + v];
-                        wave_lds_sync();
-                        accI[I][J] = accI[I][J] - mt;
+                        accI[I][J] = accI[I][J] - transposed(accI[I][J], tb);
                     } else {
                         const f32x4 p1 = accR[I][J], p2 = accI[I][J];
                         accR[I][J] = p1 + p2;
                         accI[I][J] = acc3[I][J] - p1 + p2;
                     }
                 }
+        }
+        if constexpr (KB == 2 && DIAG) {
+#pragma unroll
+            for (int I = 0; I < RB; ++I)
+                accR[I][I] = accR[I][I] + (acc3[I][I] + transposed(acc3[I][I], tb));
         }
         // accumulator element v of lane l is row 4*(l/16)+v, column l%16
 #pragma unroll
@@ -275,8 +420,9 @@ __device__ __forceinline__ void x_wave(const XArgs &a, int wave, float *tb) {
     const int f = rest % a.K;
     const int sp = rest / a.K;
     const int I0 = a.regions[reg].x, J0 = a.regions[reg].y;
-    const int kb0 = (int)((int64_t)sp * a.nkb / a.nsplit);
-    const int kb1 = (int)((int64_t)(sp + 1) * a.nkb / a.nsplit);
+    const int nst = a.nkb / XRegion<PREC, RB, DIAG>::KB;  // a whole number of steps
+    const int kb0 = (int)((int64_t)sp * nst / a.nsplit);
+    const int kb1 = (int)((int64_t)(sp + 1) * nst / a.nsplit);
     XRegion<PREC, RB, DIAG> x;
     x.zero();
     x.run(a.spec, a.K, a.a_pad, f, I0, J0, kb0, kb1);
@@ -533,6 +679,137 @@ __device__ __forceinline__ void x_chan_f32(const XArgs &a, int unit, uint4 *cons
                 X.add(pr, pc);
             });
         X.store(a.partial, obase, a.N, o.x, o.y, tbw);
+    }
+}
+
+// Float records as halves: the same wave roles, steps of two k-blocks.  Every
+// block is used by four or five waves, so it is split into halves once, by the
+// wave that loads it: a wave's own two blocks come by direct loads into its part
+// of a raw buffer (two of them: the loads run two steps ahead, and no barrier is
+// needed before a wave reads what it loaded itself), and their halves go to the
+// buffer (two in turn) that every wave multiplies from, with one barrier a step.
+// Waves w and w + 4 share a SIMD: one splits the next step's blocks before its
+// products, the other after them, so that one's products run beside the other's
+// vector work.  The bound is the matrix cores': 136 block pairs x 6 products of 16
+// cycles over 4 SIMDs per 16 spectra, a quarter of the f32 instructions' time.
+// N = 256, K = 512, 16384 spectra: 12.7 ms with the f32 products, 6.13 ms with
+// every wave splitting the blocks it multiplies, 5.84 ms so (matrix cores 68%
+// busy, at the 1.7 GHz that the chip keeps under this load; 2.9 TB/s of records).
+constexpr int kXHalvesRaw = kXChanWaves * 4 * 64;  // uint4 per raw buffer
+constexpr int kXHalvesBuf = kXSlots * 2 * 64;      // uint4 per buffer of halves
+
+__device__ __forceinline__ void xh_issue(const uint4 *spec, int K, int a_pad, int f, int st, uint4 *raw, int wave) {
+    const int lane = threadIdx.x & 63;
+    const uint4 *rec = spec + ((int64_t)(st >> 1) * K + f) * kTQB * a_pad + (st & 1) * 8 * a_pad +
+                       (lane >> 4) * a_pad + (lane & 15) + wave * 32;
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            __builtin_amdgcn_global_load_lds(rec + q * 4 * a_pad + i * 16, raw + (wave * 4 + 2 * q + i) * 64, 16, 0, 0);
+}
+
+// The wave's own records have landed (the caller has waited).  Read in one asm
+// block with its wait: from the builtin reads the compiler, which cannot tell the
+// two raw buffers' loads apart across the loop, would wait for both.
+__device__ __forceinline__ void xh_split(const uint4 *raw, uint4 *hv, int wave, float m1) {
+    typedef const __attribute__((address_space(3))) uint4 *lds_ptr;
+    const int lane = threadIdx.x & 63;
+    const uint32_t at = (uint32_t)(uintptr_t)(lds_ptr)(raw + wave * 4 * 64 + lane);
+    i32x4 r[4];
+    asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:1024\n\t"
+                 "ds_read_b128 %2, %4 offset:2048\n\tds_read_b128 %3, %4 offset:3072\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
+                 : "v"(at)
+                 : "memory");
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const Halves v = split_records(__builtin_bit_cast(uint4, r[i]), __builtin_bit_cast(uint4, r[2 + i]), m1);
+        hv[((2 * wave + i) * 2) * 64 + lane] = v.h;
+        hv[((2 * wave + i) * 2 + 1) * 64 + lane] = v.l;
+    }
+}
+
+// Steps [st0, st1), st0 < st1, of one wave: compute(hv) runs its regions on one
+// step.  FIRST: it splits before its products.
+template <bool FIRST, typename C>
+__device__ __forceinline__ void xh_loop(const uint4 *spec, int K, int a_pad, int f, int st0, int st1, int wave, float m1,
+                                        uint4 *raw0, uint4 *raw1, uint4 *hv0, uint4 *hv1, C &&compute) {
+    const int last = st1 - 1;
+    // the blocks of step s + 1 split, and the loads of step s + 3 into the raw
+    // buffer they came from (loads past the range repeat the last step)
+    auto next = [&](int s, uint4 *raw, uint4 *hv) {
+        wait_vm_lgkm0(4);
+        xh_split(raw, hv, wave, m1);  // raw has been read
+        xh_issue(spec, K, a_pad, f, min(s + 3, last), raw, wave);
+    };
+    auto step = [&](int s, uint4 *raw, uint4 *hvn, const uint4 *hv) {
+        if constexpr (FIRST) next(s, raw, hvn);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(hv);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!FIRST) next(s, raw, hvn);
+        // this wave's reads of hv and writes of hvn are done
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_s_barrier();
+    };
+    xh_issue(spec, K, a_pad, f, st0, raw0, wave);
+    xh_issue(spec, K, a_pad, f, min(st0 + 1, last), raw1, wave);
+    next(st0 - 1, raw0, hv0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    __builtin_amdgcn_s_barrier();
+    int s = st0;
+#pragma unroll 1
+    for (; s + 1 < st1; s += 2) {
+        step(s, raw1, hv1, hv0);
+        step(s + 1, raw0, hv0, hv1);
+    }
+    if (s < st1) step(s, raw1, hv1, hv0);
+    wait_vm_lgkm0(0);  // the last loads have landed
+}
+
+__device__ __forceinline__ void x_chan_halves(const XArgs &a, int unit, uint4 *raw0, uint4 *raw1, uint4 *hv0, uint4 *hv1,
+                                              float *tb) {
+    if (unit >= a.K * a.nsplit) return;  // the whole workgroup
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int f = unit % a.K, sp = unit / a.K;
+    const int nst = a.nkb / 2;
+    const int st0 = (int)((int64_t)sp * nst / a.nsplit);
+    const int st1 = (int)((int64_t)(sp + 1) * nst / a.nsplit);
+    const int64_t obase = ((int64_t)sp * a.K + f) * a.nb;
+    const float m1 = opaque_m1();
+    auto block = [&](const uint4 *hv, int b) {
+        return Halves{lds_record(hv + (2 * b) * 64 + lane), lds_record(hv + (2 * b + 1) * 64 + lane)};
+    };
+    if (wave < 4) {
+        const int rD = 4 * wave;
+        const int2 h = xc_half(wave);
+        XRegion<kFP32H, 4, true> D;
+        XRegion<kFP32H, 4, false, 2> H;
+        D.zero();
+        H.zero();
+        if (st0 < st1)
+            xh_loop<true>(a.spec, a.K, a.a_pad, f, st0, st1, wave, m1, raw0, raw1, hv0, hv1, [&](const uint4 *hv) {
+                auto drow = [&](int I) { return block(hv, rD + I); };
+                add_halves<4, true, 4, false>(drow, drow, D.accR, D.accI, D.acc3);
+                // one region's operands at a time
+                __builtin_amdgcn_sched_barrier(0);
+                add_halves<4, false, 2, false>([&](int I) { return block(hv, h.x + I); },
+                                               [&](int J) { return block(hv, h.y + J); }, H.accR, H.accI, H.acc3);
+            });
+        D.store(a.partial, obase, a.N, rD, rD, tb + wave * 16 * 17);
+        H.store(a.partial, obase, a.N, h.x, h.y, nullptr);
+    } else {
+        const int2 o = xc_off(wave);
+        XRegion<kFP32H, 4, false> X;
+        X.zero();
+        if (st0 < st1)
+            xh_loop<false>(a.spec, a.K, a.a_pad, f, st0, st1, wave, m1, raw0, raw1, hv0, hv1, [&](const uint4 *hv) {
+                add_halves<4, false, 4, false>([&](int I) { return block(hv, o.x + I); },
+                                               [&](int J) { return block(hv, o.y + J); }, X.accR, X.accI, X.acc3);
+            });
+        X.store(a.partial, obase, a.N, o.x, o.y, nullptr);
     }
 }
 
