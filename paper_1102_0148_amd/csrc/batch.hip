@@ -10,7 +10,7 @@
 // with an agent-scope acquire, which carries the data across the XCDs' L2
 // caches.
 #include "dump_dev.h"
-#include "fstage_dev.h"
+#include "fstage_reg_dev.h"
 #include "xstage_dev.h"
 
 namespace corr {
@@ -25,10 +25,17 @@ constexpr int dga(int M, int prec) {
 template <int M, int PREC>
 __device__ __noinline__ void f_range(const FArgs &fa, int t0, int t1, char *lds) {
     constexpr int GA = dga(M, PREC);
-    using Sh = FShape<M, PREC, GA, false>;
-    float2 *zbuf = reinterpret_cast<float2 *>(lds);
-    uint32_t *bbuf = reinterpret_cast<uint32_t *>(lds + (Sh::NF * Sh::SLOT * 8 + 15) / 16 * 16);
-    f_tiles<M, PREC, GA>(fa, t0, 1, t1, zbuf, bbuf);
+    if constexpr (reg_fft<M, PREC>()) {
+        uint4 *ops = reinterpret_cast<uint4 *>(lds);
+        reg_load_ops<M>(fa, ops);
+        __syncthreads();
+        reg_units<M, PREC>(fa, t0, t1, ops);
+    } else {
+        using Sh = FShape<M, PREC, GA, false>;
+        float2 *zbuf = reinterpret_cast<float2 *>(lds);
+        uint32_t *bbuf = reinterpret_cast<uint32_t *>(lds + (Sh::NF * Sh::SLOT * 8 + 15) / 16 * 16);
+        f_tiles<M, PREC, GA>(fa, t0, 1, t1, zbuf, bbuf);
+    }
 }
 
 template <int M>
@@ -144,7 +151,11 @@ __global__ __launch_bounds__(256, 2) void batch_kernel(const BJob *jobs, const u
             }
             case BI_SCALES:
                 for (int e = it.a0 + (int)threadIdx.x; e < it.a1; e += 256)
-                    j.scales[e] = scale_one(j.p.power, j.nparts, j.p.a_pad, j.K, j.W, e, kI8CodesPerRms);
+                {
+                    const float sc = scale_one(j.p.power, j.nparts, j.p.a_pad, j.K, j.W, e, kI8CodesPerRms);
+                    j.scales[e] = sc;
+                    if (j.scales_p) j.scales_p[reg_scale_index(j.K, e / j.K, e % j.K)] = sc;
+                }
                 break;
             case BI_F: {
                 FArgs fa = j.f;
@@ -201,6 +212,7 @@ __global__ __launch_bounds__(256, 2) void batch_kernel(const BJob *jobs, const u
 
 template <int M, int PREC>
 constexpr int f_lds() {
+    if (reg_fft<M, PREC>()) return kRegLds * 16;
     return f_lds_bytes<M, PREC, dga(M, PREC), false>();
 }
 

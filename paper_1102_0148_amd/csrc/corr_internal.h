@@ -86,6 +86,8 @@ struct FArgs {
     uint4 *spec;              // records, index rec_index(c, tq, a, M, a_pad)
     float *power;             // power mode: partial sums [nwg_per_group][a_pad][M]
     const float *scales;      // int8: [N][M]
+    const float *scales_p;    // the same in the register transform's order (reg_scale_index)
+    const uint4 *ops;         // the register transform's operands (kRegOps)
     const float2 *tw;         // W_M^j (j < M), W_2M^q (q < M/2), then M zero bytes
     unsigned long long *sat;  // int8 saturation counter
     unsigned *ticket;         // records mode: 8 tile-chunk counters, zero at launch
@@ -97,6 +99,28 @@ struct FArgs {
     int ntiles;               // ntq_used * ngroups (normal mode)
     int tiles_per_wg;         // power mode: time tiles per workgroup
 };
+
+// The register transform (fstage_reg_dev.h; reduced-precision records at M = 256 and
+// 512): its matrix operands in f16 halves, one 16-byte entry per lane: [f][re hi, re
+// lo, im hi, im lo][lane] of the first product, then [re hi, re lo, im hi, im lo][lane]
+// of the second product for columns c > 0 and for column 0.
+constexpr int kRegOps = (16 + 2) * 4 * 64;
+constexpr size_t kRegOpsBytes = (size_t)kRegOps * 16;
+__host__ __device__ constexpr bool uses_reg_fft(int M, int prec) { return (M == 256 || M == 512) && prec != kFP32; }
+// Where the scale of (antenna a, channel ch) lies for its lanes: [a][half][d][c mod
+// 4][c / 4], ch = the first half's bin of column c and lane column d, or (M = 512) the
+// second half's, 512 minus that.
+__host__ __device__ inline int64_t reg_scale_index(int M, int a, int ch) {
+    int half = 0, k = ch;
+    if (M == 512 && ch >= 256) {
+        half = 1;
+        k = ch == 256 ? 0 : 512 - ch;
+    }
+    const int r = k % 32;
+    const int c = k % 16 == 0 ? 0 : r < 16 ? r : 32 - r;
+    const int d = c == 0 ? k / 16 : r < 16 ? k / 32 : (512 - c - k) / 32;
+    return (((int64_t)a * (M / 256) + half) * 16 + d) * 16 + (c % 4) * 4 + c / 4;
+}
 
 // Tile-chunk ticket counters of the records-mode F-stage: one per XCD, each on
 // its own 128-byte line.
@@ -114,6 +138,10 @@ hipError_t launch_fstage(int M, int prec, int ga, int power_mode, const FArgs &a
 int fstage_lds_bytes(int M, int prec, int ga);
 // antennas per tile that fill exactly one round of transforms
 int fstage_default_group(int M, int prec);
+// antennas per tile as run: the register transform's units are of one size
+inline int fstage_run_group(int M, int prec, int f_group) {
+    return uses_reg_fft(M, prec) ? fstage_default_group(M, prec) : f_group;
+}
 
 // ---------------------------------------------------------------- X-stage
 // A group of X regions that share their antenna blocks (large N, regions of
@@ -268,8 +296,10 @@ hipError_t launch_dump(int prec, const void *partial, double2 *acc, int nsplit, 
 // power divides by W spectra, or by *w_valid when given (the spectra of the
 // window that arrived, counted on the device by the frame ingest), and by the
 // channel's non-zero components (1 for DC, else 2); scale = codes_per_rms / rms.
+// scales_p (may be null): the same once more in the register transform's order.
 hipError_t launch_scales(const float *power, int nparts, int N, int a_pad, int K, int W,
-                         const unsigned *w_valid, float codes_per_rms, float *scales, hipStream_t st);
+                         const unsigned *w_valid, float codes_per_rms, float *scales, float *scales_p,
+                         hipStream_t st);
 // dst[bl][f] = acc[f][bl] (raw layout), then acc = 0.
 hipError_t launch_finalize(double2 *acc, double2 *dst, int K, int nb, hipStream_t st);
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t st);
@@ -294,7 +324,7 @@ struct BJob {
     FArgs p;             // calibration power sums (int8)
     XArgs xd, xo;        // X-stage over the diagonal / off-diagonal regions
     double2 *acc;        // integration buffer [K][nb]
-    float *scales;
+    float *scales, *scales_p;
     int K, prec, rb_d, rb_o;
     int n_acc;           // K * nb
     int W, nparts;       // calibration window and power partials

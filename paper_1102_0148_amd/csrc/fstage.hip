@@ -1,5 +1,5 @@
 // Single-job F-stage kernels over the device functions of fstage_dev.h.
-#include "fstage_dev.h"
+#include "fstage_reg_dev.h"
 
 namespace corr {
 namespace {
@@ -51,6 +51,41 @@ __global__ __launch_bounds__(kThreads) void fstage_track_kernel(FArgs args) {
     f_records<M, PREC, GA, true>(args, zbuf, bbuf);
 }
 
+// Records by the register transform: two workgroups per CU (two wavefronts a SIMD, 256
+// registers each; the workgroup's 74 KB of operands).
+template <int M, int PREC, bool TRACK>
+__global__ __launch_bounds__(kThreads, 2) void fstage_reg_kernel(FArgs kargs) {
+    // as in fstage_kernel
+    typedef const __attribute__((address_space(1))) uint8_t *gptr;
+    FArgs args = kargs;
+    if (args.in_slot)
+        args.in = (const uint8_t *)*reinterpret_cast<const gptr *>(args.in_slot) + (int64_t)args.s_base * args.N * M;
+    __shared__ __attribute__((aligned(16))) uint4 lds[kRegLds];
+    reg_load_ops<M>(args, lds);
+    __syncthreads();
+    __shared__ int s_tk[2];
+    const int sets = args.ntiles / 4;  // a chunk has a multiple of 4 time records
+    const int t8 = (sets + 7) / 8;
+    const int x = blockIdx.x % 8;
+    const int lo = x * t8, hi = min(lo + t8, sets);
+    reg_units_dyn<M, PREC, TRACK>(args, lo, hi, args.ticket + kTicketStride * x, s_tk, lds);
+}
+
+template <int M, int PREC, bool TRACK>
+hipError_t launch_reg(const FArgs &a, hipStream_t st) {
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    // two workgroups per CU, no more than one per set of units
+    const int cap = 2 * cus / 8 > 0 ? 2 * cus / 8 : 1;
+    const int need = (a.ntiles + 31) / 32;
+    const int grid = 8 * (need < cap ? need : cap);
+    if ((e = launch_fill_zero(a.ticket, kTicketBytes, st)) != hipSuccess) return e;
+    hipLaunchKernelGGL((fstage_reg_kernel<M, PREC, TRACK>), dim3(grid), dim3(kThreads), 0, st, a);
+    return hipGetLastError();
+}
+
 template <int M, int PREC, int GA, bool POWER>
 hipError_t launch_one(const FArgs &a, int grid, hipStream_t st) {
     if constexpr (FShape<M, PREC, GA, POWER>::LDS > 160 * 1024) {
@@ -87,7 +122,8 @@ hipError_t launch_one(const FArgs &a, int grid, hipStream_t st) {
 template <int M, int PREC>
 hipError_t launch_mp(int ga, int power, const FArgs &a, int grid, hipStream_t st) {
     if (power) return launch_one<M, kFP32, power_group(M), true>(a, grid, st);
-    switch (ga) {
+    if constexpr (reg_fft<M, PREC>()) return a.track ? launch_reg<M, PREC, true>(a, st) : launch_reg<M, PREC, false>(a, st);
+    else switch (ga) {
         case 1: return launch_one<M, PREC, 1, false>(a, grid, st);
         case 2: return launch_one<M, PREC, 2, false>(a, grid, st);
         case 4: return launch_one<M, PREC, 4, false>(a, grid, st);

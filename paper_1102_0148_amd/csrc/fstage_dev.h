@@ -163,8 +163,7 @@ __device__ __forceinline__ void pass_twiddles(int j, int p, const float2 *twM, f
 
 // A lane's twiddles for every pass after the first: radix 16 (8 for M = 128)
 // after 16 points, then radix 2 (M = 512) or 4 (M = 1024) after 256.  They
-// depend only on the lane, so a workgroup loads them once.  (M = 256 runs on
-// the matrix cores and holds their operands instead.)
+// depend only on the lane, so a workgroup loads them once.
 template <int M>
 struct PassTw {
     static constexpr int R2 = M == 128 ? 8 : 16;
@@ -179,184 +178,19 @@ struct PassTw {
     }
 };
 
-// The 256-point transform on the matrix cores.  With z[16 s + f] (s, f < 16)
-//   Y[f][c]     = sum_s W16^(s c) z[16 s + f],
-//   Y'[f][c]    = W256^(f c) Y[f][c],
-//   Z[c + 16 d] = sum_f W16^(f d) Y'[f][c],
-// both 16-point DFTs are real 16 x 32 by 32 x 16 products, one transform per
-// wavefront at a time, on v_mfma_f32_16x16x32_f16: lane (j = lane mod 16,
-// g = lane / 16) holds row j of the left operand and column j of the right
-// one over contraction positions 8g .. 8g + 7, i.e. the real parts of points
-// 4g .. 4g + 3, then their imaginary parts, and gets rows 4g + i of column j
-// of the result.  The real form of
-// W16 in that layout is the same register set in both products: the right
-// operand of the first (contraction s, column c = j) and the left operand of
-// the second (row d = j, contraction f).  Each DFT is summed from f16 halves,
-// W16 = hi + lo and Y' = hi + lo, with the products of halves exact in the
-// f32 accumulator; the dropped lo * lo terms and the rounding of the lo
-// halves are of order 2^-21 of the result.  The 4-bit samples are exact in
-// f16.  Bins 0 and 128 see only the entries +-1 and 0 (hi exact, lo zero) and
-// stay exact.  The first product's result is already the second one's right
-// operand in the same lanes: no exchange between the passes.
-//
-// The 512-point transform is one radix-2 step (decimation in time) after two
-// such transforms of the even and the odd samples, E and O:
-//   Z[q] = E[q] + W512^q O[q],  Z[q + 256] = E[q] - W512^q O[q],  q < 256,
-// where lane (j, g) already holds E and O at the same q = j + 16 (4g + i).
 typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
 typedef float f4_t __attribute__((ext_vector_type(4)));
 
-// The matrix-core transform serves the reduced-precision records at 256 and
-// 512 points, where the F-stage is bound by vector work.  The float32 records
-// (bound by their HBM writes, where it measured a few percent slower) and the
-// calibration power sums keep the vector transform.
-template <int M, int PREC> constexpr bool mfma_fft() { return (M == 256 || M == 512) && PREC != kFP32; }
-
-template <int M>
-struct MfmaFft {
-    static constexpr int P = M / 256;  // 256-point transforms per block
-    h8_t dh[2], dl[2];  // W16, real form: [0] real outputs, [1] imaginary outputs
-    float2 w[4];        // W256^(f c), f = 4g + i, c = j
-    float2 w2[P == 2 ? 4 : 1];  // W512^q, q = j + 16 (4g + i)
-    uint32_t sel01[P], sel23[P];
-    // -1, opaque to the optimizer: a known -1 turns the product of the
-    // split's fma into a subtraction, which has no mixed-precision form
-    float m1;
-    __device__ __forceinline__ void load(int, const float2 *twM) {
-        const int lane = threadIdx.x & 63, j = lane & 15, g = lane >> 4;
-        m1 = -1.0f;
-        asm volatile("" : "+v"(m1));
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int s = 4 * g + i;
-            // twM[e] = exp(-2 pi i e / M) = (cos t, -sin t); the real form of
-            // multiplication by it is [cos t, sin t] -> re, [-sin t, cos t] -> im
-            const float2 t = twM[((s * j) & 15) * (M / 16)];
-            const float v[2][2] = {{t.x, -t.y}, {t.y, t.x}};
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const _Float16 h = (_Float16)v[b][c];
-                    dh[b][4 * c + i] = h;
-                    dl[b][4 * c + i] = (_Float16)(v[b][c] - (float)h);
-                }
-            w[i] = twM[((s * j) & 255) * (M / 256)];
-            if constexpr (P == 2) w2[i] = twM[j + 16 * s];
-        }
-        // byte b of four dwords -> one dword: b = j mod 4 (256 points), or
-        // 2 (j mod 2) + p for the even (p = 0) and odd (p = 1) samples
-#pragma unroll
-        for (int p = 0; p < P; ++p) {
-            const uint32_t b = P == 1 ? (j & 3) : 2 * (j & 1) + p;
-            sel01[p] = b | (b + 4) << 8 | 0x0c0c0000u;
-            sel23[p] = 0x0c0cu | b << 16 | (b + 4) << 24;
-        }
-    }
-};
+// The reduced-precision records at 256 and 512 points are transformed in registers
+// on the matrix cores (fstage_reg_dev.h).  The float32 records (bound by their HBM
+// writes) and the calibration power sums, whose f32 precision f16 halves do not
+// reach, keep the vector transform here.
+template <int M, int PREC> constexpr bool reg_fft() { return (M == 256 || M == 512) && PREC != kFP32; }
 
 __device__ __forceinline__ f4_t mfma_h(h8_t a, h8_t b, f4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
-
-// 256 points, the lane's four samples z[16 (4g + i) + j] packed one per byte
-// of p, to the lane's four outputs Z[j + 16 (4g + i)] (zr, zi).
-template <int M>
-__device__ __forceinline__ void dft256_mfma(uint32_t p, const MfmaFft<M> &k, f4_t &zr, f4_t &zi) {
-    // offset nibbles u = n + 8 as 1024 + u in f16 (byte u under the exponent
-    // byte 0x64), then minus 1032: exact.  Real parts are the low nibbles.
-    const uint32_t t = p ^ 0x88888888u;
-    const uint32_t lo = t & 0x0f0f0f0fu, hi = (t >> 4) & 0x0f0f0f0fu;
-    const uint32_t bits[4] = {__builtin_amdgcn_perm(0x64646464u, lo, 0x04010400u),
-                              __builtin_amdgcn_perm(0x64646464u, lo, 0x04030402u),
-                              __builtin_amdgcn_perm(0x64646464u, hi, 0x04010400u),
-                              __builtin_amdgcn_perm(0x64646464u, hi, 0x04030402u)};
-    h8_t a;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        const h2_t v = __builtin_bit_cast(h2_t, bits[w]) - h2_t{(_Float16)1032.0f, (_Float16)1032.0f};
-        a[2 * w] = v[0];
-        a[2 * w + 1] = v[1];
-    }
-    const f4_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
-    f4_t yr = mfma_h(a, k.dl[0], zero), yi = mfma_h(a, k.dl[1], zero);
-    yr = mfma_h(a, k.dh[0], yr);
-    yi = mfma_h(a, k.dh[1], yi);
-    float2 y[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) y[i] = cmul(make_float2(yr[i], yi[i]), k.w[i]);
-    // hi: y rounded toward zero to f16, i.e. cut to 11 significant bits
-    // (below 2^-14 the cut is coarser, by at most 2^-24), lo = y - hi, exact
-    // in the f32 arithmetic of the mixed-precision fma, rounded to f16; real
-    // parts at positions 0-3, imaginary parts at 4-7
-    h8_t bh, bl;
-#pragma unroll
-    for (int i = 0; i < 4; i += 2) {
-        const h2_t hr = __builtin_bit_cast(h2_t, __builtin_amdgcn_cvt_pkrtz(y[i].x, y[i + 1].x));
-        const h2_t hm = __builtin_bit_cast(h2_t, __builtin_amdgcn_cvt_pkrtz(y[i].y, y[i + 1].y));
-        bh[i] = hr[0];
-        bh[i + 1] = hr[1];
-        bh[4 + i] = hm[0];
-        bh[4 + i + 1] = hm[1];
-        bl[i] = (_Float16)__builtin_fmaf((float)hr[0], k.m1, y[i].x);
-        bl[i + 1] = (_Float16)__builtin_fmaf((float)hr[1], k.m1, y[i + 1].x);
-        bl[4 + i] = (_Float16)__builtin_fmaf((float)hm[0], k.m1, y[i].y);
-        bl[4 + i + 1] = (_Float16)__builtin_fmaf((float)hm[1], k.m1, y[i + 1].y);
-    }
-    zr = mfma_h(k.dl[0], bh, zero);
-    zi = mfma_h(k.dl[1], bh, zero);
-    zr = mfma_h(k.dh[0], bl, zr);
-    zi = mfma_h(k.dh[1], bl, zi);
-    zr = mfma_h(k.dh[0], bh, zr);
-    zi = mfma_h(k.dh[1], bh, zi);
-}
-
-// The wavefront's T transforms of a round: bytes from the staging bb (dword
-// d of a block at (d mod M/64) 16 + d div M/64, so that lane (j, g) finds the
-// bytes it needs, z[16 s + j] (256) or z[32 s + 2j + p] (512) for s = 4g ..
-// 4g + 3, at one byte of four consecutive dwords) to Z in slot z[t].  All
-// reads come first and all writes last, so the transforms' products and
-// vector work interleave.
-template <int M, int T>
-__device__ __forceinline__ void fft_mfma(const uint32_t *bb, float2 *const (&z)[T], const MfmaFft<M> &k) {
-    constexpr int P = MfmaFft<M>::P;
-    const int lane = threadIdx.x & 63, j = lane & 15, g = lane >> 4;
-    uint4 w[T];
-#pragma unroll
-    for (int t = 0; t < T; ++t)
-        w[t] = *reinterpret_cast<const uint4 *>(bb + t * (M / 4) + (j / (64 / (M / 16))) * 16 + 4 * g);
-    f4_t zr[T][P], zi[T][P];
-#pragma unroll
-    for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int p = 0; p < P; ++p) {
-            const uint32_t b = __builtin_amdgcn_perm(w[t].y, w[t].x, k.sel01[p]) |
-                               __builtin_amdgcn_perm(w[t].w, w[t].z, k.sel23[p]);
-            dft256_mfma<M>(b, k, zr[t][p], zi[t][p]);
-        }
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-        if (z[t] == nullptr) continue;  // idle slot (wave-uniform)
-        if constexpr (P == 1) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) z[t][pad(j + 16 * (4 * g + i))] = make_float2(zr[t][0][i], zi[t][0][i]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int q = j + 16 * (4 * g + i);
-                const float2 e = make_float2(zr[t][0][i], zi[t][0][i]);
-                const float2 o = cmul(make_float2(zr[t][1][i], zi[t][1][i]), k.w2[i]);
-                z[t][pad(q)] = cadd(e, o);
-                z[t][pad(q + 256)] = csub(e, o);
-            }
-        }
-    }
-}
-
-// The per-lane constants of a transform of M points for records of PREC.
-template <int M, int PREC>
-using FftConsts = typename std::conditional<mfma_fft<M, PREC>(), MfmaFft<M>, PassTw<M>>::type;
 
 // Signed nibble at bit offset `off` of w.
 __device__ __forceinline__ float nib(uint32_t w, int off) {
@@ -391,6 +225,15 @@ __device__ __forceinline__ void quantise(const float (&x)[NV], float sc, float l
             qm[t] = __builtin_amdgcn_fmed3f(qm[t], kMagic - lim, kMagic + lim);
         }
     }
+}
+
+// From the biased code 1.5 * 2^23 + q: words whose low bytes are the base-255 digits
+// h and l of q (see make_record).
+__device__ __forceinline__ void int16_digit_bits(float qm, uint32_t &h, uint32_t &l) {
+    constexpr float kMagic = 12582912.0f;
+    const float hm = fmaf(qm - kMagic, 1.0f / 255.0f, kMagic);
+    h = __float_as_uint(hm);
+    l = __float_as_uint(qm) + __float_as_uint(hm);
 }
 
 // Pack TS spectra of one (channel, antenna) into a 16-byte record
@@ -429,18 +272,13 @@ __device__ __forceinline__ uint4 make_record(const float *re, const float *im, f
         // biased floats is therefore (q + h) mod 256, which is
         // (q - 255 h) mod 256 = l mod 256, the byte the record holds.
         // Record: [h of re x4][h of im x4][l of re x4][l of im x4].
-        constexpr float kMagic = 12582912.0f;
         uint32_t hb[8], lb[8];
         float x[8], qm[8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) x[t] = t < 4 ? re[t] : im[t - 4];
         quantise<8>(x, sc, (float)kI16Max, wsat, qm);
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const float hm = fmaf(qm[t] - kMagic, 1.0f / 255.0f, kMagic);
-            hb[t] = __float_as_uint(hm);
-            lb[t] = __float_as_uint(qm[t]) + __float_as_uint(hm);
-        }
+        for (int t = 0; t < 8; ++t) int16_digit_bits(qm[t], hb[t], lb[t]);
         uint32_t w[4];
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
@@ -537,7 +375,7 @@ __device__ __forceinline__ void load_tile(const FArgs &args, int tq, int g, u32x
 // (ts * GA + ga).
 template <int M, int PREC, int NF, int ROUNDS>
 __device__ __forceinline__ void tile_ffts(const u32x4 (&raw)[ROUNDS], float2 *zbuf, uint32_t *bbuf,
-                                          const FftConsts<M, PREC> &tw) {
+                                          const PassTw<M> &tw) {
     constexpr int L = M / 16, FPR = kThreads / L, SLOT = M + M / 16 + 1;
     const int fs = threadIdx.x / L, j = threadIdx.x % L;
     uint32_t *bb = bbuf + fs * (M / 4);
@@ -551,60 +389,39 @@ __device__ __forceinline__ void tile_ffts(const u32x4 (&raw)[ROUNDS], float2 *zb
             bb[(d % (L / 4)) * 16 + d / (L / 4)] = w[c];
         }
     };
-    if constexpr (mfma_fft<M, PREC>()) {
-        // Every lane takes part (the matrix products need the whole
-        // wavefront): the bytes of idle slots are the zero page's, and the
-        // wavefront runs its own slots of the round one at a time.
-        constexpr int W = 64 / L;
-        const int f0 = (threadIdx.x >> 6) * W;
 #pragma unroll
-        for (int r = 0; r < ROUNDS; ++r) {
-            stage(raw[r]);
-            wave_lds_sync();
-            float2 *z[W];
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int fi = r * FPR + fs;
+        if (NF < FPR && fi >= NF) break;  // idle transform slots (one round only)
+        float2 *z = zbuf + fi * SLOT;
+        stage(raw[r]);
+        wave_lds_sync();
+        // pass 1: radix 16 over z[j + r L], unpacked from the bytes
+        {
+            float2 v[16];
+            const uint4 *src = reinterpret_cast<const uint4 *>(bb + (j / 4) * 16);
+            const int off = 8 * (j & 3);
 #pragma unroll
-            for (int t = 0; t < W; ++t) {
-                const int ft = r * FPR + f0 + t;
-                z[t] = (NF % FPR == 0 || ft < NF) ? zbuf + ft * SLOT : nullptr;
-            }
-            fft_mfma<M, W>(bbuf + f0 * (M / 4), z, tw);
-            wave_lds_sync();
-        }
-    } else {
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const uint4 w4 = src[q4];
+                const uint32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
-        for (int r = 0; r < ROUNDS; ++r) {
-            const int fi = r * FPR + fs;
-            if (NF < FPR && fi >= NF) break;  // idle transform slots (one round only)
-            float2 *z = zbuf + fi * SLOT;
-            stage(raw[r]);
-            wave_lds_sync();
-            // pass 1: radix 16 over z[j + r L], unpacked from the bytes
-            {
-                float2 v[16];
-                const uint4 *src = reinterpret_cast<const uint4 *>(bb + (j / 4) * 16);
-                const int off = 8 * (j & 3);
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    const uint4 w4 = src[q4];
-                    const uint32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const uint32_t byte = w[c] >> off;
-                        v[4 * q4 + c] = make_float2(nib(byte, 0), nib(byte, 4));
-                    }
+                for (int c = 0; c < 4; ++c) {
+                    const uint32_t byte = w[c] >> off;
+                    v[4 * q4 + c] = make_float2(nib(byte, 0), nib(byte, 4));
                 }
-                dft16(v);
+            }
+            dft16(v);
 #pragma unroll
-                for (int q = 0; q < 16; ++q) z[pad(16 * j + q)] = v[q];
-            }
-            wave_lds_sync();
-            fft_pass<M, PassTw<M>::R2>(z, j, 16, tw.w2);
-            if constexpr (PassTw<M>::R3 > 1) {
-                wave_lds_sync();
-                fft_pass<M, PassTw<M>::R3>(z, j, 256, tw.w3);
-            }
-            wave_lds_sync();
+            for (int q = 0; q < 16; ++q) z[pad(16 * j + q)] = v[q];
         }
+        wave_lds_sync();
+        fft_pass<M, PassTw<M>::R2>(z, j, 16, tw.w2);
+        if constexpr (PassTw<M>::R3 > 1) {
+            wave_lds_sync();
+            fft_pass<M, PassTw<M>::R3>(z, j, 256, tw.w3);
+        }
+        wave_lds_sync();
     }
 }
 
@@ -613,7 +430,7 @@ __device__ __forceinline__ void tile_ffts(const u32x4 (&raw)[ROUNDS], float2 *zb
 template <int M, int PREC, int GA>
 struct TileConsts {
     using Sh = FShape<M, PREC, GA, false>;
-    FftConsts<M, PREC> ptw;
+    PassTw<M> ptw;
     float2 bw[Sh::TPT];
     __device__ __forceinline__ void load(const FArgs &args) {
         const int tid = threadIdx.x;
@@ -654,32 +471,46 @@ __device__ __forceinline__ void tile_scales(const FArgs &args, int g, float *slo
 // next are formed in double and reduced to [-1/2, 1/2] turns, so long
 // integrations and large delays lose nothing to the argument's size; the
 // hardware sine and cosine take turns; the record's later spectra follow by
-// complex multiplication by the step (at most 7 steps).
-template <int M, int TS>
-__device__ __forceinline__ void track_rotate(const double4 &m, int ch, int s0, float *re, float *im) {
-    const double kf = (double)ch * (1.0 / (2.0 * M));
-    const double nu = fma(kf, m.y, m.w);
-    const double rb = fma((double)s0, nu, fma(kf, m.x, m.z));
-    const float fb = (float)(rb - rint(rb));
-    float c = __builtin_amdgcn_cosf(fb), sn = __builtin_amdgcn_sinf(fb);
-    float cs = 1.0f, ss = 0.0f;
-    if constexpr (TS > 1) {
-        const float fs = (float)(nu - rint(nu));
-        cs = __builtin_amdgcn_cosf(fs);
-        ss = __builtin_amdgcn_sinf(fs);
+// complex multiplication by the step (at most 7 steps).  load() takes what
+// depends on the antenna and the first spectrum alone, in turns and turns per
+// channel, so that a channel costs one fma for each of the two phases.  (As
+// 64-bit integer fractions of a turn, which wrap by themselves, the phases were
+// slower: 512-point int8 records of 16384 spectra, N = 44, 0.36 against 0.31 ms.)
+template <int M>
+struct TrackModel {
+    double a, b, da, db;  // turns: channel ch at spectrum s0, a ch + b; per spectrum, da ch + db
+    __device__ __forceinline__ void load(const double4 &m, int s0) {
+        da = m.y * (1.0 / (2.0 * M));
+        db = m.w;
+        a = fma((double)s0, da, m.x * (1.0 / (2.0 * M)));
+        b = fma((double)s0, db, m.z);
     }
+    // TS spectra of the channel ch (as a double)
+    template <int TS>
+    __device__ __forceinline__ void rotate(double ch, float *re, float *im) const {
+        const double rb = fma(ch, a, b);
+        const float fb = (float)(rb - rint(rb));
+        float c = __builtin_amdgcn_cosf(fb), sn = __builtin_amdgcn_sinf(fb);
+        float cs = 1.0f, ss = 0.0f;
+        if constexpr (TS > 1) {
+            const double nu = fma(ch, da, db);
+            const float fs = (float)(nu - rint(nu));
+            cs = __builtin_amdgcn_cosf(fs);
+            ss = __builtin_amdgcn_sinf(fs);
+        }
 #pragma unroll
-    for (int ts = 0; ts < TS; ++ts) {
-        const float x = re[ts], y = im[ts];
-        re[ts] = x * c - y * sn;
-        im[ts] = x * sn + y * c;
-        if (ts + 1 < TS) {
-            const float c2 = c * cs - sn * ss;
-            sn = c * ss + sn * cs;
-            c = c2;
+        for (int ts = 0; ts < TS; ++ts) {
+            const float x = re[ts], y = im[ts];
+            re[ts] = fmaf(x, c, -(y * sn));
+            im[ts] = fmaf(x, sn, y * c);
+            if (ts + 1 < TS) {
+                const float c2 = fmaf(c, cs, -(sn * ss));
+                sn = fmaf(c, ss, sn * cs);
+                c = c2;
+            }
         }
     }
-}
+};
 
 // One tile (time record tq, antenna group g) of records from frames already
 // loaded: TS spectra of GA antennas transformed, turned into bins, rotated by
@@ -690,7 +521,7 @@ __device__ __forceinline__ void tile_records(const FArgs &args, int tq, int g,
                                              const u32x4 (&cur)[FShape<M, PREC, GA, false>::ROUNDS],
                                              const TileConsts<M, PREC, GA> &k, const float *slo, const float *shi,
                                              unsigned &wsat, float2 *zbuf, uint32_t *bbuf,
-                                             const double4 &trk = double4{0, 0, 0, 0}) {
+                                             const TrackModel<M> &trk = TrackModel<M>{}) {
     using Sh = FShape<M, PREC, GA, false>;
     constexpr int TS = Sh::TS, SLOT = Sh::SLOT, NTASK = Sh::NTASK, TPT = Sh::TPT;
     const int tid = threadIdx.x;
@@ -725,9 +556,8 @@ __device__ __forceinline__ void tile_records(const FArgs &args, int tq, int g,
         }
         const int clo = q, chi = q == 0 ? M / 2 : M - q;
         if constexpr (TRACK) {
-            const int s0 = args.s_base + tq * TS;
-            track_rotate<M, TS>(trk, clo, s0, lr, li);
-            track_rotate<M, TS>(trk, chi, s0, hr, hi);
+            trk.template rotate<TS>((double)clo, lr, li);
+            trk.template rotate<TS>((double)chi, hr, hi);
         }
         const uint4 rlo = make_record<PREC, TS>(lr, li, slo[it], wsat);
         const uint4 rhi = make_record<PREC, TS>(hr, hi, shi[it], wsat);
@@ -815,8 +645,8 @@ __device__ __forceinline__ void f_tiles_dyn(const FArgs &args, int lo, int hi, u
         // the thread's antenna is the same for all its tasks (kThreads is a
         // multiple of GA); loaded, like the scales, before the prefetch, so
         // waiting for it does not wait for the next tile's frames
-        double4 trk{0, 0, 0, 0};
-        if constexpr (TRACK) trk = args.track[g * GA + tid % GA];
+        TrackModel<M> trk{};
+        if constexpr (TRACK) trk.load(args.track[g * GA + tid % GA], args.s_base + tq * TS);
         u32x4 cur[ROUNDS];
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r) cur[r] = raw[r];
@@ -850,7 +680,7 @@ __device__ __forceinline__ void f_power_block(const FArgs &args, int blk, float2
     if (pg >= args.ngroups) return;
     const int tile0 = pw * args.tiles_per_wg;
     const int tile1 = min(tile0 + args.tiles_per_wg, args.ntq);
-    FftConsts<M, kFP32> ptw;
+    PassTw<M> ptw;
     ptw.load(tid % (M / 16), args.tw);
     float2 bw[TPT];
     float plo[TPT], phi[TPT];

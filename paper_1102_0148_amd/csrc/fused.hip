@@ -32,7 +32,7 @@
 // workgroup is on has all of its dependencies finished or finishable.  Waits
 // are bounded (about a second) and set the error flag when they give up, so
 // every wave always exits.
-#include "fstage_dev.h"
+#include "fstage_reg_dev.h"
 #include "xstage_dev.h"
 
 namespace corr {
@@ -85,7 +85,11 @@ __device__ __forceinline__ void fx_publish(unsigned *xcd_count, unsigned per_xcd
 }
 
 template <int M, int PREC, int GA>
-__device__ __forceinline__ void fx_f_role(const FxArgs &a, float2 *zbuf, uint32_t *bbuf, int *s_tk) {
+__device__ __forceinline__ void fx_f_role(const FxArgs &a, float2 *zbuf, uint32_t *bbuf, int *s_tk, uint4 *ops) {
+    if constexpr (reg_fft<M, PREC>()) {
+        reg_load_ops<M>(a.f, ops);
+        __syncthreads();
+    }
     const int tg = record_times(PREC);
     const int x = blockIdx.x % 8;
     const int n_xwg = (int)gridDim.x - a.n_fwg;
@@ -106,9 +110,14 @@ __device__ __forceinline__ void fx_f_role(const FxArgs &a, float2 *zbuf, uint32_
         fa.S = Sc;
         const int ntq_used = ((Sc + tg - 1) / tg + step_records(PREC) - 1) / step_records(PREC) * step_records(PREC);
         fa.ntiles = ntq_used * fa.ngroups;
-        const int t8 = (fa.ntiles + 7) / 8;
-        const int lo = x * t8, hi = min(lo + t8, fa.ntiles);
-        f_tiles_dyn<M, PREC, GA>(fa, lo, hi, cc + kTicketStride * x, s_tk, zbuf, bbuf);
+        // (the register transform's tickets are sets of four units)
+        const int ntk = reg_fft<M, PREC>() ? fa.ntiles / 4 : fa.ntiles;
+        const int t8 = (ntk + 7) / 8;
+        const int lo = x * t8, hi = min(lo + t8, ntk);
+        if constexpr (reg_fft<M, PREC>())
+            reg_units_dyn<M, PREC, false>(fa, lo, hi, cc + kTicketStride * x, s_tk, ops);
+        else
+            f_tiles_dyn<M, PREC, GA>(fa, lo, hi, cc + kTicketStride * x, s_tk, zbuf, bbuf);
         fx_publish(cc + kFxXcdDone + kTicketStride * x, (unsigned)(a.n_fwg / 8), cc + kFxDone);
     }
 }
@@ -154,16 +163,18 @@ __device__ __forceinline__ void fx_x_role(const FxArgs &a, int xrank, float *tb)
 // Workgroups per CU the kernel's registers are bounded to: up to 512-point
 // transforms three, so that two of them run the F-stage beside one X
 // workgroup (four made the fp16 and int8 kernels spill); larger transforms
-// two.
-constexpr int fx_min_blocks(int M, int prec) { return M <= 256 ? 3 : 2; }
+// two, and so do the register transforms.
+constexpr int fx_min_blocks(int M, int prec) { return M <= 256 && !uses_reg_fft(M, prec) ? 3 : 2; }
 
 template <int M, int PREC, int GA, int RB>
 __global__ __launch_bounds__(kThreads, fx_min_blocks(M, PREC)) void fx_kernel(FxArgs kargs) {
     using Sh = FShape<M, PREC, GA, false>;
     static_assert(Sh::LDS <= 160 * 1024, "LDS budget");
     static_assert(Sh::NF * Sh::SLOT * 8 >= 4 * 16 * 17 * 4, "X transposes use the transform slots");
-    __shared__ float2 zbuf[Sh::NF * Sh::SLOT];
-    __shared__ __attribute__((aligned(16))) uint32_t bbuf[Sh::FPR * (M / 4)];
+    constexpr bool REG = reg_fft<M, PREC>();
+    __shared__ float2 zbuf[REG ? 4 * 16 * 17 / 2 : Sh::NF * Sh::SLOT];
+    __shared__ __attribute__((aligned(16))) uint32_t bbuf[REG ? 4 : Sh::FPR * (M / 4)];
+    __shared__ __attribute__((aligned(16))) uint4 ops[REG ? kRegLds : 1];
     __shared__ int s_tk[2];
     const FxArgs &a = kargs;
     const int b = blockIdx.x;
@@ -178,7 +189,7 @@ __global__ __launch_bounds__(kThreads, fx_min_blocks(M, PREC)) void fx_kernel(Fx
         xrank = b - a.n_fwg;
     }
     if (f_role) {
-        fx_f_role<M, PREC, GA>(a, zbuf, bbuf, s_tk);
+        fx_f_role<M, PREC, GA>(a, zbuf, bbuf, s_tk, ops);
     } else {
         float *tb = reinterpret_cast<float *>(zbuf) + (threadIdx.x >> 6) * 16 * 17;
         fx_x_role<PREC, RB>(a, xrank, tb);

@@ -103,6 +103,46 @@ void fill_twiddles(float2 *tw, int K) {
     for (int q = 0; q < K / 2; ++q) tw[K + q] = twiddle(q, 2 * K);
 }
 
+// The register transform's operands (corr_internal.h, kRegOps), the same for every
+// channel count it serves; made once per process.
+void split_f16(double v, _Float16 *hi, _Float16 *lo) {
+    *hi = (_Float16)v;
+    *lo = (_Float16)(v - (double)*hi);
+}
+const std::vector<_Float16> &reg_operands() {
+    static const std::vector<_Float16> table = [] {
+        std::vector<double> cs(512), sn(512);
+        for (int q = 0; q < 512; ++q) cos_sin_2pi(q, 512, &cs[q], &sn[q]);
+        std::vector<_Float16> t((size_t)kRegOps * 8);
+        // entry `at` (a lane's 8 positions) of the operands at at (hi) and at + 64 (lo)
+        auto put = [&](size_t at, int pos, double v) { split_f16(v, &t[at * 8 + pos], &t[(at + 64) * 8 + pos]); };
+        for (int f = 0; f < 16; ++f)
+            for (int lane = 0; lane < 64; ++lane)
+                for (int pos = 0; pos < 8; ++pos) {
+                    const int c = lane % 16, s = 8 * (pos % 4) + 2 * (lane / 16) + pos / 4;
+                    const int q = c * (16 * s + f) % 512;
+                    put((size_t)(4 * f) * 64 + lane, pos, c ? cs[q] : (s % 2 == 0 ? 1.0 : 0.0));
+                    put((size_t)(4 * f + 2) * 64 + lane, pos, c ? -sn[q] : (s % 2 == 1 ? 1.0 : 0.0));
+                }
+        for (int lane = 0; lane < 64; ++lane)
+            for (int pos = 0; pos < 8; ++pos) {
+                const int d = lane % 16, f = 4 * (lane / 16) + pos % 4, part = pos / 4;
+                // columns c > 0: multiplication by W16^(f d), conjugated for d >= 8
+                const int q = 32 * (f * d % 16);
+                const double sign = d >= 8 ? -1.0 : 1.0;
+                put((size_t)64 * 64 + lane, pos, part ? sn[q] : cs[q]);
+                put((size_t)66 * 64 + lane, pos, sign * (part ? cs[q] : -sn[q]));
+                // column 0: the 32-point transform of p[f], p[f + 16]; bin 256 (the
+                // alternating sum) in the imaginary part of bin 0
+                const int r = f + 16 * part, q0 = 16 * (r * d % 32);
+                put((size_t)68 * 64 + lane, pos, cs[q0]);
+                put((size_t)70 * 64 + lane, pos, d ? -sn[q0] : (r % 2 ? -1.0 : 1.0));
+            }
+        return t;
+    }();
+    return table;
+}
+
 struct Timer {
     int stage;
     hipEvent_t a, b;
@@ -130,7 +170,9 @@ struct corr_ctx {
     double2 *acc = nullptr;
     double2 *stage = nullptr;
     float2 *tw = nullptr;
+    uint4 *ops = nullptr;       // the register transform's operands
     float *scales = nullptr;
+    float *scales_p = nullptr;  // the scales in the register transform's order
     float *power = nullptr;
     bool scales_valid = false;  // a calibration has been enqueued into `scales`
     int2 *regions = nullptr;
@@ -219,7 +261,7 @@ void free_ctx(corr_ctx *h) {
     void *bufs[] = {h->spec,    h->partial, h->acc,     h->stage,   h->tw,     h->scales,
                     h->power,   h->regions, h->sat,     h->fticket, h->xgroups, h->bjobs,
                     h->in_ptrs, h->items,   h->bctr,    h->track,   h->ingest_owner, h->ingest_ctr,
-                    h->fx_ctr,  h->fx_err};
+                    h->fx_ctr,  h->fx_err,  h->ops,     h->scales_p};
     for (void *p : bufs)
         if (p) hipFree(p);
     for (corr_ctx *j : h->jobs) free_ctx(j);
@@ -275,23 +317,29 @@ int plan_fused(corr_ctx *h) {
     if (cus % 8) return fail(CORR_EINVAL, "the fused pipeline expects the CUs in 8 XCDs (%d CUs)", cus);
     h->fx_grid = per_cu * cus;
     h->fx_cus = cus;
-    int x_waves = 0;
-    if (h->fx_fcus) {
-        // split layout: whole CUs per role, f_cus of each XCD's CUs run F
-        if (h->fx_fcus >= cus / 8)
-            return fail(CORR_EINVAL, "f_cus_per_xcd=%d out of [1, %d] (%d CUs per XCD)", h->fx_fcus, cus / 8 - 1, cus / 8);
-        h->fx_nfwg = 8 * h->fx_fcus * per_cu;
-        x_waves = 4 * (cus - 8 * h->fx_fcus) * per_cu;
-    } else {
-        const int fpc = h->fx_fpc ? h->fx_fpc : per_cu - 1;
-        if (fpc < 1 || fpc >= per_cu)
-            return fail(CORR_EINVAL, "f_workgroups_per_cu=%d out of [1, %d] (%d workgroups per CU)", fpc, per_cu - 1,
-                        per_cu);
-        h->fx_nfwg = fpc * cus;
-        x_waves = 4 * (per_cu - fpc) * cus;
-    }
-    h->fx_nsplit = std::max(1, std::min(64, x_waves / h->K));
+    // The register transform's kernels keep two workgroups per CU (72 KB of
+    // operands and 256 registers), the other forms' three or more.  Their
+    // layout arguments are taken as for three and cut to what two can run.
+    const int arg_per_cu = uses_reg_fft(h->K, h->prec) ? std::max(per_cu, 3) : per_cu;
+    int fcus = h->fx_fcus, fpc = h->fx_fpc ? h->fx_fpc : arg_per_cu - 1;
+    if (fcus >= cus / 8)
+        return fail(CORR_EINVAL, "f_cus_per_xcd=%d out of [1, %d] (%d CUs per XCD)", fcus, cus / 8 - 1, cus / 8);
+    if (!fcus && fpc >= arg_per_cu)
+        return fail(CORR_EINVAL, "f_workgroups_per_cu=%d out of [1, %d] (%d workgroups per CU)", fpc, arg_per_cu - 1,
+                    arg_per_cu);
+    // split layout: whole CUs per role, fcus of each XCD's CUs run F
+    const auto waves = [&](int n) { return fcus ? 4 * (cus - 8 * fcus) * n : 4 * (n - fpc) * cus; };
+    const int arg_waves = waves(arg_per_cu);
+    if (h->K > arg_waves)
+        return fail(CORR_EINVAL, "the fused pipeline needs %d X waves for K=%d, has %d", h->K, h->K, arg_waves);
+    const int arg_nsplit = std::max(1, std::min(64, arg_waves / h->K));
+    fpc = std::min(fpc, per_cu - 1);
+    while (fcus > 1 && h->K > waves(per_cu)) --fcus;
+    const int x_waves = waves(per_cu);
     if (h->K > x_waves) return fail(CORR_EINVAL, "the fused pipeline needs %d X waves for K=%d, has %d", h->K, h->K, x_waves);
+    h->fx_nfwg = fcus ? 8 * fcus * per_cu : fpc * cus;
+    h->fx_fcus = fcus;
+    h->fx_nsplit = std::max(1, std::min(64, x_waves / h->K));
     // chunks: records of a slot about 72 MB, so a ring of three stays in the
     // 256 MB Infinity Cache (N = 44 fp32: 768 spectra, measured the fastest of
     // 512, 768 and 1024)
@@ -299,18 +347,23 @@ int plan_fused(corr_ctx *h) {
     int chunk = h->fx_chunk;
     if (!chunk) chunk = (int)std::max<int64_t>(64, ((int64_t)72 << 20) / per_spectrum / 64 * 64);
     chunk = (int)std::min<int64_t>(chunk, round_up64(h->S, 64));
+    // a partial sums at most 2048 (fp32) / 16384 (fp16) spectra; int8 sums
+    // are exact over the whole integration
+    const int cap = h->prec == kFP32 ? kF32SplitSpectra : h->prec == kFP16 ? kF16SplitSpectra : 0;
+    const auto unit_spectra = [&](int nsplit) {
+        const int kb_chunk = (chunk + 4 * h->TG - 1) / (4 * h->TG);
+        return (kb_chunk + nsplit - 1) / nsplit * 4 * h->TG;
+    };
+    if (cap && unit_spectra(arg_nsplit) > cap)
+        return fail(CORR_EINVAL, "chunk_spectra=%d gives %d spectra per partial in one chunk, above %d", chunk,
+                    unit_spectra(arg_nsplit), cap);
+    if (cap) chunk = std::min(chunk, h->fx_nsplit * cap);
+    const int per_unit = unit_spectra(h->fx_nsplit);
     h->fx_nchunks = (h->S + chunk - 1) / chunk;
     h->fx_ring = std::max(1, std::min(h->fx_ring ? h->fx_ring : 3, h->fx_nchunks));
     const int ntq_slot = round_up((chunk + h->TG - 1) / h->TG, kTQB);
     h->fx_slot_recs = (int64_t)h->K * ntq_slot * h->a_pad;
-    // a partial sums at most 2048 (fp32) / 16384 (fp16) spectra; int8 sums
-    // are exact over the whole integration
-    const int kb_chunk = (chunk + 4 * h->TG - 1) / (4 * h->TG);
-    const int per_unit = (kb_chunk + h->fx_nsplit - 1) / h->fx_nsplit * 4 * h->TG;
-    const int cap = h->prec == kFP32 ? kF32SplitSpectra : h->prec == kFP16 ? kF16SplitSpectra : 0;
     h->fx_flush = cap ? std::max(1, cap / per_unit) : h->fx_nchunks;
-    if (cap && per_unit > cap)
-        return fail(CORR_EINVAL, "chunk_spectra=%d gives %d spectra per partial in one chunk, above %d", chunk, per_unit, cap);
     const int epochs = (h->fx_nchunks + h->fx_flush - 1) / h->fx_flush;
     h->fx_nslots = epochs * h->fx_nsplit;
     h->tiles.chunk_spectra = chunk;
@@ -335,6 +388,16 @@ int alloc_calibration(corr_ctx *h) {
     const int nparts = (ntq_w + kCalibTilesPerWG - 1) / kCalibTilesPerWG;
     HIP_TRY(hipMalloc(&h->scales, (size_t)h->N * h->K * sizeof(float)), "hipMalloc(scales)");
     HIP_TRY(hipMalloc(&h->power, (size_t)nparts * h->a_pad * h->K * sizeof(float)), "hipMalloc(power)");
+    if (uses_reg_fft(h->K, h->prec))
+        HIP_TRY(hipMalloc(&h->scales_p, (size_t)h->N * h->K * sizeof(float)), "hipMalloc(scales)");
+    return CORR_OK;
+}
+
+// The register transform's operands on the device.
+int alloc_operands(corr_ctx *h) {
+    if (!uses_reg_fft(h->K, h->prec)) return CORR_OK;
+    HIP_TRY(hipMalloc(&h->ops, kRegOpsBytes), "hipMalloc(operands)");
+    HIP_TRY(hipMemcpy(h->ops, reg_operands().data(), kRegOpsBytes, hipMemcpyHostToDevice), "hipMemcpy(operands)");
     return CORR_OK;
 }
 
@@ -345,6 +408,7 @@ int plan(corr_ctx *h) {
     if (h->pipeline == CORR_PIPELINE_FUSED) {
         int rc = plan_fused(h);
         if (!rc) rc = alloc_calibration(h);
+        if (!rc) rc = alloc_operands(h);
         if (rc) return rc;
         h->planned = true;
         return CORR_OK;
@@ -376,6 +440,7 @@ int plan(corr_ctx *h) {
     HIP_TRY(hipMalloc(&h->partial, (size_t)h->tiles.x_splits * h->K * h->nb * (h->prec == kINT16 ? 16 : 8)),
             "hipMalloc(partials)");
     int rc = alloc_calibration(h);
+    if (!rc) rc = alloc_operands(h);
     if (rc) return rc;
     h->planned = true;
     return CORR_OK;
@@ -503,7 +568,7 @@ int calibrate(corr_ctx *h, const uint8_t *in, hipStream_t st) {
     // after a frame ingest, the spectra of the window that arrived
     const unsigned *w_valid = h->ingest_pending ? h->ingest_ctr + 3 : nullptr;
     const float fs = h->prec == kINT16 ? kI16CodesPerRms : kI8CodesPerRms;
-    HIP_TRY(launch_scales(h->power, nparts, h->N, h->a_pad, h->K, W, w_valid, fs, h->scales, st),
+    HIP_TRY(launch_scales(h->power, nparts, h->N, h->a_pad, h->K, W, w_valid, fs, h->scales, h->scales_p, st),
             "scales launch");
     h->scales_valid = true;
     timer_end(h, st);
@@ -518,7 +583,7 @@ int process_one(corr_ctx *h, const uint8_t *in, hipStream_t st) {
         if (rc) return rc;
     }
     const int chunk = h->tiles.chunk_spectra;
-    const int ga = h->tiles.f_group;
+    const int ga = fstage_run_group(h->K, h->prec, h->tiles.f_group);
     const int ngroups = (h->N + ga - 1) / ga;
     const int64_t frame = (int64_t)h->N * h->K;
     if (h->track_on && h->track_dirty) {
@@ -535,6 +600,8 @@ int process_one(corr_ctx *h, const uint8_t *in, hipStream_t st) {
         fx.f.in = in;
         fx.f.spec = h->spec;
         fx.f.scales = h->scales;
+        fx.f.scales_p = h->scales_p;
+        fx.f.ops = h->ops;
         fx.f.tw = h->tw;
         fx.f.sat = h->sat;
         fx.f.N = h->N;
@@ -582,6 +649,8 @@ int process_one(corr_ctx *h, const uint8_t *in, hipStream_t st) {
         fa.s_base = c0;
         fa.spec = h->spec;
         fa.scales = h->scales;
+        fa.scales_p = h->scales_p;
+        fa.ops = h->ops;
         fa.tw = h->tw;
         fa.sat = h->sat;
         fa.ticket = h->fticket;
@@ -1195,6 +1264,8 @@ int batch_build(corr_ctx *b) {
         std::memset(&d, 0, sizeof d);
         d.f.spec = h->spec;
         d.f.scales = h->scales;
+        d.f.scales_p = h->scales_p;
+        d.f.ops = h->ops;
         d.f.tw = h->tw;
         d.f.sat = h->sat;
         d.f.N = h->N;
@@ -1221,6 +1292,7 @@ int batch_build(corr_ctx *b) {
         d.xo.nregions = h->n_off;
         d.acc = h->acc;
         d.scales = h->scales;
+        d.scales_p = h->scales_p;
         d.K = h->K;
         d.prec = h->prec;
         d.rb_d = rb;
@@ -1249,7 +1321,8 @@ int batch_build(corr_ctx *b) {
         }
         // longer F items amortise each item's fixed costs (twiddles, the first
         // frames' latency, the publish) once a job has tiles to spare
-        const int tpi = std::max(kBatchTilesPerItem, std::min(kBatchMaxTilesPerItem, d.f.ntiles / 1024));
+        // (a multiple of 4: the register transform takes units in fours)
+        const int tpi = std::max(kBatchTilesPerItem, std::min(kBatchMaxTilesPerItem, d.f.ntiles / 1024)) / 4 * 4;
         int n_f = 0;
         for (int t = 0; t < d.f.ntiles; t += tpi, ++n_f)
             fitems[j].push_back(BItem{BI_F, j, t, std::min(t + tpi, d.f.ntiles), h->prec == kINT8 ? c0 + 1 : -1,
@@ -1392,8 +1465,10 @@ int corr_batch_read_scales(corr_handle b, int job, float *out) {
 //   [32 KB, 33 KB)   F-stage tile tickets (cleared by every F-stage launch)
 //   [33 KB, ...)     saturation counter (only ever added to)
 //   [36 KB, 44 KB)   region table, [44 KB, 48 KB) region groups (per call)
-//   [64 KB, end)     per call: integration buffer, power partials (int8 /
+//   [64 KB, 256 MB)  per call: integration buffer, power partials (int8 /
 //                    int16), X-stage partials, spectra records + slack
+//   [256 MB, +72 KB) the register transform's operands (written once at set-up)
+//   then             per call: the scales in that transform's order
 // Calls that overlap on one GPU share the array and race.
 
 namespace {
@@ -1404,10 +1479,14 @@ constexpr size_t kScrSat = kScrTicket + kTicketBytes;
 constexpr size_t kScrRegions = (size_t)36 << 10;
 constexpr size_t kScrGroups = (size_t)44 << 10;
 constexpr size_t kScrHeader = (size_t)64 << 10;
+constexpr size_t kScrOps = kScratchBytes;
+constexpr size_t kScrScalesP = kScrOps + kRegOpsBytes;
+constexpr size_t kScrArray = kScratchBytes + ((size_t)2 << 20);
 constexpr int kScrMaxDevices = 64;
 static_assert(kScrSat + 8 <= kScrRegions, "scratch header overlap");
 static_assert(kScrRegions + 528 * sizeof(int2) <= kScrGroups, "region table exceeds its slot");
 static_assert(kScrGroups + 10 * sizeof(XGroup) <= kScrHeader, "group table exceeds its slot");
+static_assert(kScrScalesP + (size_t)CORR_MAX_ANTENNAS * 512 * sizeof(float) <= kScrArray, "reordered scales exceed their slot");
 
 // Offset of the twiddle table of K channels: tables for K = 128, 256, ...
 // each rounded up to 256 bytes.
@@ -1419,7 +1498,7 @@ size_t scr_tw_offset(int K) {
 
 }  // namespace
 
-static __device__ __align__(256) uint8_t scratch[kScratchBytes];
+static __device__ __align__(256) uint8_t scratch[kScrArray];
 
 namespace {
 
@@ -1444,6 +1523,8 @@ int scratch_setup(uint8_t **out) {
         for (int K = CORR_MIN_CHANNELS; K <= CORR_MAX_CHANNELS; K *= 2)
             fill_twiddles(tw + scr_tw_offset(K) / sizeof(float2), K);
         HIP_TRY(hipMemcpy(p, tw, sizeof tw, hipMemcpyHostToDevice), "hipMemcpy(scratch twiddles)");
+        HIP_TRY(hipMemcpy(static_cast<uint8_t *>(p) + kScrOps, reg_operands().data(), kRegOpsBytes, hipMemcpyHostToDevice),
+                "hipMemcpy(scratch operands)");
         g_scr[dev] = static_cast<uint8_t *>(p);
     }
     *out = g_scr[dev];
@@ -1551,6 +1632,8 @@ extern "C" int corr_process_noalloc(int N, int K, int n_spectra, int precision, 
     h.acc = reinterpret_cast<double2 *>(base + off_acc);
     h.power = power_bytes ? reinterpret_cast<float *>(base + off_power) : nullptr;
     h.scales = is_quant(precision) ? scales : nullptr;
+    h.scales_p = is_quant(precision) && uses_reg_fft(K, precision) ? reinterpret_cast<float *>(base + kScrScalesP) : nullptr;
+    h.ops = reinterpret_cast<uint4 *>(base + kScrOps);
     h.partial = base + off_part;
     h.spec = reinterpret_cast<uint4 *>(base + off_spec);
     h.tiles.chunk_spectra = chunk;
