@@ -23,13 +23,42 @@ __global__ __launch_bounds__(256) void scales_kernel(const float *power, int npa
     if (scales_p) scales_p[reg_scale_index(K, e / K, e % K)] = sc;
 }
 
-// dst[bl][f] = acc[f][bl]; acc = 0
-__global__ __launch_bounds__(256) void finalize_kernel(double2 *acc, double2 *dst, int K, int nb) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= (int64_t)K * nb) return;
-    const int f = (int)(e / nb), bl = (int)(e % nb);
-    dst[(int64_t)bl * K + f] = acc[e];
-    acc[e] = make_double2(0.0, 0.0);
+// dst[bl][f] = acc[f][bl]; acc = 0.  Bound by memory: 48 bytes an element.  A
+// tile of 64 baselines by 16 channels is turned through LDS, so that a
+// wavefront reads (and clears) 1 KB of a channel's row and writes 256 bytes of
+// a baseline's; written straight, each lane of a wavefront wrote to a line of
+// its own.  The tiles of a channel row follow each other on one XCD (workgroup
+// b runs on XCD b % 8), since rows of nb 16-byte elements start inside a line.
+// N = 256, K = 512: 416 -> 161 us (5.0 TB/s, a large copy's rate; 176 us
+// without the order of tiles, 170 us in 64 x 32 tiles, 212 us in 16 x 64);
+// N = 44, K = 256: 5.4 -> 3.5 us.
+constexpr int kFinB = 64, kFinF = 16;
+
+__global__ __launch_bounds__(256) void finalize_kernel(double2 *acc, double2 *dst, int K, int nb, int ntb, int ntiles) {
+    __shared__ double2 tile[kFinF][kFinB + 1];
+    const int lb = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    if (lb >= ntiles) return;
+    const int b0 = lb % ntb * kFinB, f0 = lb / ntb * kFinF;
+    constexpr int R = kFinB * kFinF / 256, RF = 256 / kFinB, RB = 256 / kFinF;
+    const int x = threadIdx.x % kFinB, y = threadIdx.x / kFinB;
+    if (b0 + x < nb) {
+        double2 *p = acc + (int64_t)(f0 + y) * nb + b0 + x;
+        double2 v[R];
+#pragma unroll
+        for (int i = 0; i < R; ++i) v[i] = p[(int64_t)i * RF * nb];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            tile[y + i * RF][x] = v[i];
+            p[(int64_t)i * RF * nb] = make_double2(0.0, 0.0);
+        }
+    }
+    __syncthreads();
+    const int f = threadIdx.x % kFinF, b = threadIdx.x / kFinF;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int bl = b0 + b + i * RB;
+        if (bl < nb) dst[(int64_t)bl * K + f0 + f] = tile[f][b + i * RB];
+    }
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(uint4 *p, int64_t n16) {
@@ -65,9 +94,10 @@ hipError_t launch_scales(const float *power, int nparts, int N, int a_pad, int K
 }
 
 hipError_t launch_finalize(double2 *acc, double2 *dst, int K, int nb, hipStream_t st) {
-    const int64_t n = (int64_t)K * nb;
-    const int grid = (int)((n + 255) / 256);
-    hipLaunchKernelGGL(finalize_kernel, dim3(grid), dim3(256), 0, st, acc, dst, K, nb);
+    static_assert(128 % kFinF == 0, "K, a multiple of 128, is whole tiles");
+    const int ntb = (nb + kFinB - 1) / kFinB, ntiles = ntb * (K / kFinF);
+    const int grid = 8 * ((ntiles + 7) / 8);  // workgroups past the end exit
+    hipLaunchKernelGGL(finalize_kernel, dim3(grid), dim3(256), 0, st, acc, dst, K, nb, ntb, ntiles);
     return hipGetLastError();
 }
 

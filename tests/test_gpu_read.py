@@ -1,0 +1,56 @@
+"""The read-out's tiles of baselines and channels, and where an asynchronous read may go."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1102_0148_amd as corr
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+# 3, 55, 66, 136 and 990 baselines: less than a tile of 64, one short of it, past it, past
+# two, many; reads into device memory, at an 8-byte offset of it, and pinned memory
+@pytest.mark.parametrize("N,K", [(2, 128), (10, 1024), (11, 256), (16, 512), (44, 128)])
+def test_async_read_destinations(N, K):
+    S, n = 40, N * (N + 1) // 2 * K * 2
+    x = synth.packed(synth.recipe_plain(N=N, two_k=2 * K, rho=0.3, seed=N), 0, S).contiguous().cuda()
+    c = corr.Correlator(N, K, S)
+    c.process(x)
+    ref = c.read_cps_raw().reshape(-1)
+    wide = torch.full((n + 2,), 7.53, dtype=torch.float64, device="cuda")
+    pinned = torch.empty(n, dtype=torch.float64, pin_memory=True)
+    for dst in (wide[:n], wide[1:n + 1], wide[2:], pinned):
+        wide.fill_(7.53)
+        c.process(x)
+        c.read_cps_async(dst)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(dst.cpu().numpy(), ref)
+        if dst is not pinned:
+            assert (wide == 7.53).sum().item() == 2  # nothing beside it
+    c.process(x)  # the buffer was cleared each time
+    np.testing.assert_array_equal(c.read_cps_raw().reshape(-1), ref)
+    c.close()
+
+
+def test_captured_process_and_read_replays():
+    N, K, S = 11, 256, 70
+    xs = [synth.packed(synth.recipe_plain(N=N, two_k=2 * K, rho=0.3, seed=s), 0, S).contiguous().cuda() for s in range(3)]
+    c = corr.Correlator(N, K, S)
+    refs = []
+    for x in xs:
+        c.process(x)
+        refs.append(c.read_cps_raw().reshape(-1))
+    x = xs[0].clone()
+    dst = torch.zeros(refs[0].size, dtype=torch.float64, device="cuda")
+    s, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        c.process(x)
+        c.read_cps_async(dst)
+    for i in (0, 1, 2, 1):
+        x.copy_(xs[i])
+        dst.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(dst.cpu().numpy(), refs[i])
