@@ -334,7 +334,7 @@ int corr_batch_read_scales(corr_handle b, int job, float *out);
  * corr_read_cps_raw, with no handle and no allocation: every buffer beyond
  * the caller's input and outputs (records, partials, the float64 integration
  * buffer, calibration sums, tickets, twiddle and region tables) lives in one
- * static device array of 258 MiB per GPU, held until the process ends.  The
+ * static device array of 257 MiB per GPU, held until the process ends.  The
  * integration runs in chunks of spectra cut to fit that array (for N = 44,
  * K = 256: 2304 spectra in FP32, 9088 in INT8), so FP32 / FP16 results
  * agree with corr_process within their tolerance and INT8 / INT16 sums are

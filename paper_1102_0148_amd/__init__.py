@@ -420,7 +420,7 @@ class Correlator:
     def read_cps(self) -> np.ndarray:
         out = np.empty((self.nb, self.K, 2), dtype=np.float32)
         corr_read_cps(self.h, _np_ptr(out))
-        return out[..., 0] + 1j * out[..., 1]
+        return out.view(np.complex64)[..., 0]
 
     def read_cps_async(self, dst, stream=None):
         """dst: float64 CUDA tensor with nb*K*2 elements."""
@@ -598,7 +598,7 @@ class Batch:
         N, K, _, _ = self.jobs[j]
         out = np.empty((n_baselines(N), K, 2), dtype=np.float32)
         corr_batch_read_cps(self.h, j, _np_ptr(out))
-        return out[..., 0] + 1j * out[..., 1]
+        return out.view(np.complex64)[..., 0]
 
     def read_scales(self, j: int) -> np.ndarray:
         N, K, _, _ = self.jobs[j]

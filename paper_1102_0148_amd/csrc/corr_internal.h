@@ -302,6 +302,8 @@ hipError_t launch_scales(const float *power, int nparts, int N, int a_pad, int K
                          hipStream_t st);
 // dst[bl][f] = acc[f][bl] (raw layout), then acc = 0.
 hipError_t launch_finalize(double2 *acc, double2 *dst, int K, int nb, hipStream_t st);
+// The same as float2, divided by the antennas' scales [N][K] unless null.
+hipError_t launch_finalize_float(double2 *acc, float2 *dst, const float *scales, int N, int K, int nb, hipStream_t st);
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t st);
 
 // ---------------------------------------------------------------- ingest

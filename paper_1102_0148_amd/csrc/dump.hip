@@ -32,10 +32,22 @@ __global__ __launch_bounds__(256) void scales_kernel(const float *power, int npa
 // N = 256, K = 512: 416 -> 161 us (5.0 TB/s, a large copy's rate; 176 us
 // without the order of tiles, 170 us in 64 x 32 tiles, 212 us in 16 x 64);
 // N = 44, K = 256: 5.4 -> 3.5 us.
+// As float2 the sums leave in float, divided by their antennas' scales where
+// there are any: in double, as a host loop over the doubles did.
 constexpr int kFinB = 64, kFinF = 16;
 
-__global__ __launch_bounds__(256) void finalize_kernel(double2 *acc, double2 *dst, int K, int nb, int ntb, int ntiles) {
-    __shared__ double2 tile[kFinF][kFinB + 1];
+// First antenna of baseline bl of N antennas (row a starts at a N - a (a - 1) / 2).
+__device__ __forceinline__ int first_antenna(int bl, int N) {
+    int a = (int)((2 * N + 1 - sqrtf((float)((2 * N + 1) * (2 * N + 1) - 8 * bl))) * 0.5f);
+    while (a > 0 && a * N - a * (a - 1) / 2 > bl) --a;
+    while ((a + 1) * N - (a + 1) * a / 2 <= bl) ++a;
+    return a;
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void finalize_kernel(double2 *acc, T *dst, const float *scales, int N, int K, int nb,
+                                                       int ntb, int ntiles) {
+    __shared__ T tile[kFinF][kFinB + 1];
     const int lb = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
     if (lb >= ntiles) return;
     const int b0 = lb % ntb * kFinB, f0 = lb / ntb * kFinF;
@@ -46,9 +58,24 @@ __global__ __launch_bounds__(256) void finalize_kernel(double2 *acc, double2 *ds
         double2 v[R];
 #pragma unroll
         for (int i = 0; i < R; ++i) v[i] = p[(int64_t)i * RF * nb];
+        if constexpr (sizeof(T) == sizeof(float2)) {
+            if (scales) {
+                const int a = first_antenna(b0 + x, N), b = b0 + x - (a * N - a * (a - 1) / 2) + a;
+                const float *sa = scales + (int64_t)a * K + f0 + y, *sb = scales + (int64_t)b * K + f0 + y;
+#pragma unroll
+                for (int i = 0; i < R; ++i) {
+                    const double d = (double)sa[i * RF] * (double)sb[i * RF];
+                    v[i].x /= d;
+                    v[i].y /= d;
+                }
+            }
+        }
 #pragma unroll
         for (int i = 0; i < R; ++i) {
-            tile[y + i * RF][x] = v[i];
+            if constexpr (sizeof(T) == sizeof(float2))
+                tile[y + i * RF][x] = make_float2((float)v[i].x, (float)v[i].y);
+            else
+                tile[y + i * RF][x] = v[i];
             p[(int64_t)i * RF * nb] = make_double2(0.0, 0.0);
         }
     }
@@ -93,12 +120,25 @@ hipError_t launch_scales(const float *power, int nparts, int N, int a_pad, int K
     return hipGetLastError();
 }
 
-hipError_t launch_finalize(double2 *acc, double2 *dst, int K, int nb, hipStream_t st) {
+namespace {
+
+template <typename T>
+hipError_t launch_finalize_as(double2 *acc, T *dst, const float *scales, int N, int K, int nb, hipStream_t st) {
     static_assert(128 % kFinF == 0, "K, a multiple of 128, is whole tiles");
     const int ntb = (nb + kFinB - 1) / kFinB, ntiles = ntb * (K / kFinF);
     const int grid = 8 * ((ntiles + 7) / 8);  // workgroups past the end exit
-    hipLaunchKernelGGL(finalize_kernel, dim3(grid), dim3(256), 0, st, acc, dst, K, nb, ntb, ntiles);
+    hipLaunchKernelGGL(finalize_kernel<T>, dim3(grid), dim3(256), 0, st, acc, dst, scales, N, K, nb, ntb, ntiles);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_finalize(double2 *acc, double2 *dst, int K, int nb, hipStream_t st) {
+    return launch_finalize_as<double2>(acc, dst, nullptr, 0, K, nb, st);
+}
+
+hipError_t launch_finalize_float(double2 *acc, float2 *dst, const float *scales, int N, int K, int nb, hipStream_t st) {
+    return launch_finalize_as<float2>(acc, dst, scales, N, K, nb, st);
 }
 
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t st) {

@@ -54,3 +54,29 @@ def test_captured_process_and_read_replays():
         g.replay()
         torch.cuda.synchronize()
         np.testing.assert_array_equal(dst.cpu().numpy(), refs[i])
+
+
+# float reads: the GPU's conversion and descaling against the raw sums', tiles as above; the
+# last has more bytes than leave through pinned memory
+@pytest.mark.parametrize("prec", ["fp32", "int8", "int16"])
+@pytest.mark.parametrize("N,K", [(2, 128), (11, 256), (44, 512), (96, 1024)])
+def test_float_read_is_the_descaled_raw_read(N, K, prec):
+    S = 40
+    x = synth.packed(synth.recipe_plain(N=N, two_k=2 * K, rho=0.3, seed=N), 0, S).contiguous().cuda()
+    c = corr.Correlator(N, K, S, precision=prec)
+    c.process(x)
+    raw = c.read_cps_raw()
+    c.process(x)
+    got = c.read_cps()
+    ref = raw.reshape(-1, K, 2)
+    if prec != "fp32":
+        sc = c.read_scales().astype(np.float64)
+        i, j = np.triu_indices(N)
+        ref = ref / (sc[i] * sc[j])[..., None]
+    assert got.shape == (N * (N + 1) // 2, K) and got.dtype == np.complex64
+    np.testing.assert_array_equal(np.stack([got.real, got.imag], -1), ref.astype(np.float32))
+    with pytest.raises(corr.CorrError):  # taken
+        c.read_cps()
+    c.process(x)
+    np.testing.assert_array_equal(c.read_cps(), got)
+    c.close()
