@@ -218,12 +218,21 @@ hipError_t launch_xgroups(int prec, const XArgs &a, hipStream_t st) {
 namespace {
 
 // int16: regions of at most 3 blocks on the diagonal and 2 off it (six
-// accumulators per block pair).
+// accumulators per block pair).  More than one region to a channel: all in
+// one launch, neighbouring waves sharing the channel's records.
 template <int RB, int KIND>
 __global__ __launch_bounds__(256, 2) void xstage16_kernel(XArgs a) {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lb = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
-    x_wave16<RB, KIND == kDiag>(a, lb * 4 + w);
+    const int wave = lb * 4 + w;
+    if constexpr (KIND == kBoth) {
+        if (wave % a.nregions < a.n_diag)
+            x_wave16<RB, true>(a, wave);
+        else
+            x_wave16<RB, false>(a, wave);
+    } else {
+        x_wave16<RB, KIND == kDiag>(a, wave);
+    }
 }
 
 template <int RB, int KIND>
@@ -243,10 +252,10 @@ hipError_t launch_xstage16(int rb, int kind, const XArgs &a, hipStream_t st) {
             case 2: return launch16<2, kDiag>(a, st);
             case 3: return launch16<3, kDiag>(a, st);
         }
-    } else if (kind == kOffDiag) {
+    } else if (kind == kBoth) {
         switch (rb) {
-            case 1: return launch16<1, kOffDiag>(a, st);
-            case 2: return launch16<2, kOffDiag>(a, st);
+            case 1: return launch16<1, kBoth>(a, st);
+            case 2: return launch16<2, kBoth>(a, st);
         }
     }
     return hipErrorInvalidValue;
