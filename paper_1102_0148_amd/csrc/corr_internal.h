@@ -90,7 +90,7 @@ struct FArgs {
     const uint4 *ops;         // the register transform's operands (kRegOps)
     const float2 *tw;         // W_M^j (j < M), W_2M^q (q < M/2), then M zero bytes
     unsigned long long *sat;  // int8 saturation counter
-    unsigned *ticket;         // records mode: 8 tile-chunk counters, zero at launch
+    unsigned *ticket;         // records mode: 8 tile-chunk counters, zero at launch (launch_dump clears them)
     const double4 *track;     // tracking model per antenna (a_pad entries), or null
     int s_base;               // integration index of the chunk's first spectrum
     int N, a_pad, S;          // S = spectra in this chunk
@@ -290,8 +290,10 @@ int fused_group(int M, int prec);
 
 // ---------------------------------------------------------------- dump etc.
 // acc[f][bl] (double2) += sum over splits of partial[sp][f][bl], in split order.
-hipError_t launch_dump(int prec, const void *partial, double2 *acc, int nsplit, int K, int nb,
-                       hipStream_t st);
+// fresh: acc holds nothing yet and is written without being read.  Clears the
+// F-stage's tile tickets.
+hipError_t launch_dump(int prec, const void *partial, double2 *acc, int nsplit, int K, int nb, bool fresh,
+                       unsigned *tickets, hipStream_t st);
 // scales[a][f] from power partials summed in order over nparts; the mean
 // power divides by W spectra, or by *w_valid when given (the spectra of the
 // window that arrived, counted on the device by the frame ingest), and by the
@@ -302,7 +304,9 @@ hipError_t launch_scales(const float *power, int nparts, int N, int a_pad, int K
                          hipStream_t st);
 // dst[bl][f] = acc[f][bl] (raw layout), then acc = 0.
 hipError_t launch_finalize(double2 *acc, double2 *dst, int K, int nb, hipStream_t st);
-// The same as float2, divided by the antennas' scales [N][K] unless null.
+// The same without clearing acc.
+hipError_t launch_finalize_keep(double2 *acc, double2 *dst, int K, int nb, hipStream_t st);
+// As float2, divided by the antennas' scales [N][K] unless null.
 hipError_t launch_finalize_float(double2 *acc, float2 *dst, const float *scales, int N, int K, int nb, hipStream_t st);
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t st);
 

@@ -5,11 +5,14 @@
 namespace corr {
 namespace {
 
-template <typename P>
-__global__ __launch_bounds__(256) void dump_kernel(const P *partial, double2 *acc, int nsplit,
-                                                   int64_t n) {
+// The first workgroup also clears the F-stage's tile tickets for the next
+// launch (a launch of its own before each F-stage took 2 to 5 us of a chunk).
+template <typename P, bool FRESH>
+__global__ __launch_bounds__(256) void dump_kernel(const P *partial, double2 *acc, int nsplit, int64_t n,
+                                                   unsigned *tickets) {
+    if (blockIdx.x == 0 && threadIdx.x < 8) tickets[threadIdx.x * kTicketStride] = 0;
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e < n) dump_one<P>(partial, acc, nsplit, n, e);
+    if (e < n) dump_one<P, FRESH>(partial, acc, nsplit, n, e);
 }
 
 __global__ __launch_bounds__(256) void scales_kernel(const float *power, int nparts, int N, int a_pad,
@@ -44,7 +47,7 @@ __device__ __forceinline__ int first_antenna(int bl, int N) {
     return a;
 }
 
-template <typename T>
+template <typename T, bool CLEAR>
 __global__ __launch_bounds__(256) void finalize_kernel(double2 *acc, T *dst, const float *scales, int N, int K, int nb,
                                                        int ntb, int ntiles) {
     __shared__ T tile[kFinF][kFinB + 1];
@@ -76,7 +79,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(double2 *acc, T *dst, con
                 tile[y + i * RF][x] = make_float2((float)v[i].x, (float)v[i].y);
             else
                 tile[y + i * RF][x] = v[i];
-            p[(int64_t)i * RF * nb] = make_double2(0.0, 0.0);
+            if (CLEAR) p[(int64_t)i * RF * nb] = make_double2(0.0, 0.0);
         }
     }
     __syncthreads();
@@ -95,20 +98,29 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint4 *p, int64_t n16) {
 
 }  // namespace
 
-hipError_t launch_dump(int prec, const void *partial, double2 *acc, int nsplit, int K, int nb,
-                       hipStream_t st) {
+namespace {
+
+template <typename P>
+hipError_t launch_dump_as(const void *partial, double2 *acc, int nsplit, int K, int nb, bool fresh, unsigned *tickets,
+                          hipStream_t st) {
     const int64_t n = (int64_t)K * nb;
     const int grid = (int)((n + 255) / 256);
-    if (prec == kINT8)
-        hipLaunchKernelGGL(dump_kernel<int2>, dim3(grid), dim3(256), 0, st,
-                           reinterpret_cast<const int2 *>(partial), acc, nsplit, n);
-    else if (prec == kINT16)
-        hipLaunchKernelGGL(dump_kernel<double2>, dim3(grid), dim3(256), 0, st,
-                           reinterpret_cast<const double2 *>(partial), acc, nsplit, n);
+    if (fresh)
+        hipLaunchKernelGGL((dump_kernel<P, true>), dim3(grid), dim3(256), 0, st, reinterpret_cast<const P *>(partial), acc,
+                           nsplit, n, tickets);
     else
-        hipLaunchKernelGGL(dump_kernel<float2>, dim3(grid), dim3(256), 0, st,
-                           reinterpret_cast<const float2 *>(partial), acc, nsplit, n);
+        hipLaunchKernelGGL((dump_kernel<P, false>), dim3(grid), dim3(256), 0, st, reinterpret_cast<const P *>(partial), acc,
+                           nsplit, n, tickets);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_dump(int prec, const void *partial, double2 *acc, int nsplit, int K, int nb, bool fresh,
+                       unsigned *tickets, hipStream_t st) {
+    if (prec == kINT8) return launch_dump_as<int2>(partial, acc, nsplit, K, nb, fresh, tickets, st);
+    if (prec == kINT16) return launch_dump_as<double2>(partial, acc, nsplit, K, nb, fresh, tickets, st);
+    return launch_dump_as<float2>(partial, acc, nsplit, K, nb, fresh, tickets, st);
 }
 
 hipError_t launch_scales(const float *power, int nparts, int N, int a_pad, int K, int W,
@@ -122,12 +134,12 @@ hipError_t launch_scales(const float *power, int nparts, int N, int a_pad, int K
 
 namespace {
 
-template <typename T>
+template <typename T, bool CLEAR = true>
 hipError_t launch_finalize_as(double2 *acc, T *dst, const float *scales, int N, int K, int nb, hipStream_t st) {
     static_assert(128 % kFinF == 0, "K, a multiple of 128, is whole tiles");
     const int ntb = (nb + kFinB - 1) / kFinB, ntiles = ntb * (K / kFinF);
     const int grid = 8 * ((ntiles + 7) / 8);  // workgroups past the end exit
-    hipLaunchKernelGGL(finalize_kernel<T>, dim3(grid), dim3(256), 0, st, acc, dst, scales, N, K, nb, ntb, ntiles);
+    hipLaunchKernelGGL((finalize_kernel<T, CLEAR>), dim3(grid), dim3(256), 0, st, acc, dst, scales, N, K, nb, ntb, ntiles);
     return hipGetLastError();
 }
 
@@ -135,6 +147,10 @@ hipError_t launch_finalize_as(double2 *acc, T *dst, const float *scales, int N, 
 
 hipError_t launch_finalize(double2 *acc, double2 *dst, int K, int nb, hipStream_t st) {
     return launch_finalize_as<double2>(acc, dst, nullptr, 0, K, nb, st);
+}
+
+hipError_t launch_finalize_keep(double2 *acc, double2 *dst, int K, int nb, hipStream_t st) {
+    return launch_finalize_as<double2, false>(acc, dst, nullptr, 0, K, nb, st);
 }
 
 hipError_t launch_finalize_float(double2 *acc, float2 *dst, const float *scales, int N, int K, int nb, hipStream_t st) {

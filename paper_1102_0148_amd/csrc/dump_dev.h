@@ -10,9 +10,11 @@ namespace {
 // (Section 1: the cross power spectra are accumulated to the cadence).
 // Runs of 16 partials are loaded before any is added, so their loads are in
 // flight together (as one loop each load waited for the previous add).
-template <typename P>
+// FRESH: the buffer holds nothing yet and is written without being read.
+template <typename P, bool FRESH = false>
 __device__ __forceinline__ void dump_one(const P *partial, double2 *acc, int nsplit, int64_t n, int64_t e) {
-    double2 v = acc[e];
+    double2 v = make_double2(0.0, 0.0);
+    if (!FRESH) v = acc[e];
     int s = 0;
     for (; s + 16 <= nsplit; s += 16) {
         P p[16];

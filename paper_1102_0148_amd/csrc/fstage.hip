@@ -6,7 +6,8 @@ namespace {
 
 // Persistent workgroups; workgroup b runs on XCD b % 8 (round-robin
 // dispatch), and the tiles of XCD x are the range [x t8, (x+1) t8), dealt one
-// by one by that XCD's ticket counter: tiles in flight on one XCD are
+// by one by that XCD's ticket counter (zero at launch: the dump that follows
+// the last launch cleared it): tiles in flight on one XCD are
 // neighbours (consecutive antenna groups of nearby time records) whose
 // partial lines meet in one L2.
 template <int M, int PREC, int GA, bool TRACK>
@@ -81,7 +82,6 @@ hipError_t launch_reg(const FArgs &a, hipStream_t st) {
     const int cap = 2 * cus / 8 > 0 ? 2 * cus / 8 : 1;
     const int need = (a.ntiles + 31) / 32;
     const int grid = 8 * (need < cap ? need : cap);
-    if ((e = launch_fill_zero(a.ticket, kTicketBytes, st)) != hipSuccess) return e;
     hipLaunchKernelGGL((fstage_reg_kernel<M, PREC, TRACK>), dim3(grid), dim3(kThreads), 0, st, a);
     return hipGetLastError();
 }
@@ -106,10 +106,6 @@ hipError_t launch_one(const FArgs &a, int grid, hipStream_t st) {
             const int cap = per_cu * cus / 8 > 0 ? per_cu * cus / 8 : 1;
             const int need = (a.ntiles + 7) / 8;
             grid = 8 * (need < cap ? need : cap);
-        }
-        if (!POWER) {
-            const hipError_t z = launch_fill_zero(a.ticket, kTicketBytes, st);
-            if (z != hipSuccess) return z;
         }
         if (track)
             hipLaunchKernelGGL((fstage_track_kernel<M, PREC, GA>), dim3(grid), dim3(kThreads), 0, st, a);

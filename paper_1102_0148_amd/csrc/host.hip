@@ -270,6 +270,7 @@ struct corr_ctx {
     double2 *stage = nullptr;
     float2 *tw = nullptr;
     const uint4 *ops = nullptr; // the register transform's operands (the device's, not freed)
+    bool fresh = false;         // the next dump finds an empty buffer, not a cleared one (no-allocation calls)
     bool counted = false;       // among the pinned pool's handles
     float *scales = nullptr;
     float *scales_p = nullptr;  // the scales in the register transform's order
@@ -640,7 +641,9 @@ int launch_x_and_dump(corr_ctx *h, const uint4 *spec, int ntq, int nkb, bool own
     timer_end(h, st);
     h->launches_x++;
     timer_begin(h, 3, st);
-    HIP_TRY(launch_dump(h->prec, h->partial, h->acc, h->tiles.x_splits, h->K, h->nb, st), "dump launch");
+    HIP_TRY(launch_dump(h->prec, h->partial, h->acc, h->tiles.x_splits, h->K, h->nb, h->fresh, h->fticket, st),
+            "dump launch");
+    h->fresh = false;
     timer_end(h, st);
     return CORR_OK;
 }
@@ -729,7 +732,7 @@ int process_one(corr_ctx *h, const uint8_t *in, hipStream_t st) {
         timer_end(h, st);
         h->launches_fused++;
         timer_begin(h, 3, st);
-        HIP_TRY(launch_dump(h->prec, h->partial, h->acc, h->fx_nslots, h->K, h->nb, st), "dump launch");
+        HIP_TRY(launch_dump(h->prec, h->partial, h->acc, h->fx_nslots, h->K, h->nb, false, h->fticket, st), "dump launch");
         timer_end(h, st);
         const int last = h->fx_nchunks - 1;
         h->last_chunk = h->S - last * chunk;
@@ -936,6 +939,7 @@ corr_ctx *create_ctx(int N, int K, int S) {
     if ((e = hipMalloc(&h->sat, sizeof(unsigned long long))) != hipSuccess) return bail(e, "hipMalloc(counter)");
     if ((e = hipMemset(h->sat, 0, sizeof(unsigned long long))) != hipSuccess) return bail(e, "hipMemset(counter)");
     if ((e = hipMalloc(&h->fticket, kTicketBytes)) != hipSuccess) return bail(e, "hipMalloc(tile tickets)");
+    if ((e = hipMemset(h->fticket, 0, kTicketBytes)) != hipSuccess) return bail(e, "hipMemset(tile tickets)");
     return h;
 }
 
@@ -1608,7 +1612,7 @@ int corr_batch_read_scales(corr_handle b, int job, float *out) {
 // array:
 //   [0, 32 KB)       twiddle tables of every channel count, each followed by
 //                    its zero page (written once per device at set-up)
-//   [32 KB, 33 KB)   F-stage tile tickets (cleared by every F-stage launch)
+//   [32 KB, 33 KB)   F-stage tile tickets (cleared at the start of each call and by each dump)
 //   [33 KB, ...)     saturation counter (only ever added to)
 //   [36 KB, 44 KB)   region table, [44 KB, 48 KB) region groups (per call)
 //   [64 KB, 256 MB)  per call: integration buffer, power partials (int8 /
@@ -1675,9 +1679,11 @@ int scratch_setup(uint8_t **out) {
     return CORR_OK;
 }
 
-// The region table and region groups of one call, built on the device.
+// The region table and region groups of one call, built on the device, and
+// the F-stage's tickets cleared.
 __global__ __launch_bounds__(256) void noalloc_tables_kernel(int2 *regs, int nreg, XGroup *groups, int ngroups,
-                                                            int nr, int rb) {
+                                                            int nr, int rb, unsigned *tickets) {
+    if (threadIdx.x < 8) tickets[threadIdx.x * kTicketStride] = 0;
     for (int i = threadIdx.x; i < nreg; i += 256) regs[i] = region_at(i, nr, rb);
     for (int i = threadIdx.x; i < ngroups; i += 256) groups[i] = group_at(i, nr);
 }
@@ -1787,16 +1793,19 @@ extern "C" int corr_process_noalloc(int N, int K, int n_spectra, int precision, 
     h.spec_bytes = spec_bytes;
     h.planned = h.started = true;
     hipStream_t st = (hipStream_t)stream;
-    // Whatever the last call left: the tables of this shape, a cleared
-    // integration buffer, and records cleared so that padding antennas and
-    // padding spectra read as zeros.
+    // Whatever the last call left: the tables of this shape and cleared
+    // tickets.  The first dump writes the integration buffer without reading
+    // it.  Records need no clearing: the F-stage writes every spectrum of the
+    // records that the X-stage reads, zeros past the last one, and what the
+    // padding antennas' lines hold reaches only products of theirs, which are
+    // not stored.  (Clearing both took 41 us of an 8192-spectrum FP32 call at
+    // N = 44, K = 256.)
     hipLaunchKernelGGL(noalloc_tables_kernel, dim3(1), dim3(256), 0, st, h.regions, region_count(nr), h.xgroups,
-                       h.n_xgroups, nr, h.rb);
+                       h.n_xgroups, nr, h.rb, h.fticket);
     HIP_TRY(hipGetLastError(), "region table launch");
-    HIP_TRY(launch_fill_zero(h.acc, acc_bytes, st), "integration buffer clear");
-    HIP_TRY(launch_fill_zero(h.spec, spec_bytes, st), "records clear");
+    h.fresh = true;
     rc = process_one(&h, static_cast<const uint8_t *>(packed), st);
     if (rc) return rc;
-    HIP_TRY(launch_finalize(h.acc, reinterpret_cast<double2 *>(cps), K, h.nb, st), "finalize launch");
+    HIP_TRY(launch_finalize_keep(h.acc, reinterpret_cast<double2 *>(cps), K, h.nb, st), "finalize launch");
     return CORR_OK;
 }
