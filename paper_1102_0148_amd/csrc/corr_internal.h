@@ -129,7 +129,7 @@ constexpr size_t kTicketBytes = 8 * kTicketStride * sizeof(unsigned);
 
 // Launch the F-stage for complex length M = K (channels).  mode: 0 = spectra
 // records in precision `prec`, over as many persistent workgroups as stay
-// resident (`grid` ignored; a.ticket zeroed first, on the same stream; with
+// resident (`grid` ignored; a.ticket is zero at launch; with
 // a.track set, the records are rotated by the tracking model);
 // 1 = power sums over the calibration window (records not written), `grid`
 // blocks.  Returns hipSuccess or the error.
@@ -138,6 +138,8 @@ hipError_t launch_fstage(int M, int prec, int ga, int power_mode, const FArgs &a
 int fstage_lds_bytes(int M, int prec, int ga);
 // antennas per tile that fill exactly one round of transforms
 int fstage_default_group(int M, int prec);
+// The group that N antennas and a chunk of so many spectra get by default.
+int fstage_auto_group(int M, int prec, int N, int chunk);
 // antennas per tile as run: the register transform's units are of one size
 inline int fstage_run_group(int M, int prec, int f_group) {
     return uses_reg_fft(M, prec) ? fstage_default_group(M, prec) : f_group;

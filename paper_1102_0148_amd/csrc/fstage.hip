@@ -153,6 +153,25 @@ int fstage_default_group(int M, int prec) {
     return g < 1 ? 1 : g;
 }
 
+// Twice the antennas where a tile then still leaves two workgroups to a CU (70 KB
+// of LDS): the records of a tile fill whole lines, or more of one.  F-stage, one
+// round of transforms and two (us): fp32 K = 1024, N = 37, 3001 spectra 452 and 271,
+// N = 6, 16384 spectra 532 and 240; K = 512, N = 44, 8192 spectra 419 and 338, N = 200,
+// 4096 spectra 1095 and 773; K = 256, N = 44, 16384 spectra 351 and 320; fp16 K = 1024,
+// N = 37 322 and 212.  Not where padding to the larger group costs more (K = 256: N = 20
+// 87 and 91, N = 24 85 and 90; a third more is won back from K = 512 on: N = 9 and its
+// X-stage 501 and 500, K = 1024, N = 5 544 and 298), nor where the chip is not filled
+// (K = 512, N = 8, 64 spectra 8.4 and 10.7).  int16 and int8 at K = 1024 gain nothing
+// (N = 37 with the X-stage 377 and 381; 262 and 350).
+int fstage_auto_group(int M, int prec, int N, int chunk) {
+    const int g = fstage_default_group(M, prec);
+    if (!(prec == kFP32 && M >= 256) && !(prec == kFP16 && M == 1024)) return g;
+    const int64_t records = (chunk + record_times(prec) - 1) / record_times(prec);
+    const int one = round_up(N, g), two = round_up(N, 2 * g);
+    const bool padded = M == 256 ? two * 4 > one * 5 : two * 3 > one * 4;
+    return padded || records * (two / (2 * g)) < 512 ? g : 2 * g;
+}
+
 hipError_t launch_fstage(int M, int prec, int ga, int power_mode, const FArgs &a, int grid,
                          hipStream_t st) {
     if (!power_mode && fstage_lds_bytes(M, prec, ga) > 160 * 1024) return hipErrorInvalidValue;

@@ -510,22 +510,28 @@ int plan(corr_ctx *h) {
         return CORR_OK;
     }
     if (h->tiles.chunk_spectra == 0) h->tiles.chunk_spectra = default_chunk(h);
-    if (h->tiles.f_group == 0) h->tiles.f_group = fstage_default_group(h->K, h->prec);
-    if (h->tiles.x_splits == 0) h->tiles.x_splits = default_splits(h);
+    if (h->tiles.f_group == 0) h->tiles.f_group = fstage_auto_group(h->K, h->prec, h->N, h->tiles.chunk_spectra);
     if (fstage_lds_bytes(h->K, h->prec, h->tiles.f_group) > 160 * 1024)
         return fail(CORR_EINVAL, "f_group=%d needs more than 160 KB of LDS at K=%d in this precision",
                     h->tiles.f_group, h->K);
     const int chunk = h->tiles.chunk_spectra;
     if (h->prec == kINT16) {
-        if ((int64_t)h->tiles.x_splits * kI16SplitSpectra < chunk)
-            return fail(CORR_EINVAL, "INT16 needs x_splits >= %d for chunks of %d spectra (exact int32 digit sums)",
-                        (chunk + kI16SplitSpectra - 1) / kI16SplitSpectra, chunk);
         // six accumulators per block pair: regions of at most 3 blocks on the
         // diagonal and 2 off it
         if (h->rb > 3) {
             hipError_t e = set_regions(h, h->nblk % 2 == 0 ? 2 : 1);
             if (e != hipSuccess) return hip_fail(e, "regions");
         }
+    }
+    // for the regions as they are launched (int16, sized for 4-block regions
+    // before: N = 61, K = 512, 5001 spectra in 8 splits and in 3, X-stage and
+    // dump 230 and 219 us; N = 75, K = 256, 4096 spectra in 16 and in 2, 209
+    // and under 152 us)
+    if (h->tiles.x_splits == 0) h->tiles.x_splits = default_splits(h);
+    if (h->prec == kINT16) {
+        if ((int64_t)h->tiles.x_splits * kI16SplitSpectra < chunk)
+            return fail(CORR_EINVAL, "INT16 needs x_splits >= %d for chunks of %d spectra (exact int32 digit sums)",
+                        (chunk + kI16SplitSpectra - 1) / kI16SplitSpectra, chunk);
     }
     h->ntq_buf = round_up((chunk + h->TG - 1) / h->TG, kTQB);
     h->spec_bytes = (size_t)h->K * h->ntq_buf * h->a_pad * kRecordBytes;
@@ -1788,7 +1794,7 @@ extern "C" int corr_process_noalloc(int N, int K, int n_spectra, int precision, 
     h.spec = reinterpret_cast<uint4 *>(base + off_spec);
     h.tiles.chunk_spectra = chunk;
     h.tiles.x_splits = splits;
-    h.tiles.f_group = fstage_default_group(K, precision);
+    h.tiles.f_group = fstage_auto_group(K, precision, N, chunk);
     h.ntq_buf = round_up((chunk + h.TG - 1) / h.TG, kTQB);
     h.spec_bytes = spec_bytes;
     h.planned = h.started = true;
