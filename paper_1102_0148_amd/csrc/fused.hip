@@ -141,10 +141,12 @@ __device__ __forceinline__ void fx_x_role(const FxArgs &a, int xrank, float *tb)
         const int Sc = min(a.chunk, a.S - c * a.chunk);
         const int nst = ((Sc + tg - 1) / tg + 4 * Region::KB - 1) / (4 * Region::KB);
         if (active) {
+            // with the padding antennas (16 RB): these kernels have no registers for
+            // the addresses that leave it out
             const int kb0 = (int)((int64_t)sp * nst / a.x.nsplit);
             const int kb1 = (int)((int64_t)(sp + 1) * nst / a.x.nsplit);
-            acc.template run<(Region::KB == 2 ? 2 : kFxXBuf)>(a.f.spec + (int64_t)(c % a.ring) * a.slot_recs, a.x.K, a.x.a_pad, f, 0, 0,
-                                      kb0, kb1);
+            acc.template run<(Region::KB == 2 ? 2 : kFxXBuf)>(a.f.spec + (int64_t)(c % a.ring) * a.slot_recs, a.x.K, a.x.a_pad,
+                                                                 16 * RB, f, 0, 0, kb0, kb1);
         }
         // every load of the chunk has returned before the slot can be reused
         __builtin_amdgcn_s_waitcnt(0x0F70);

@@ -197,6 +197,14 @@ __device__ __forceinline__ void add_halves(Row &&row, Col &&col, f32x4 (&accR)[R
     }
 }
 
+// What takes a lane of block B from its antenna back to the last one, if its
+// own is padding.  A 128-byte line holds 8 antennas' records, so with N mod 16
+// in 1..8 half of the last block's lines are left out.  X-stage, these lines
+// read and not (us): N = 5, K = 1024, 8192 spectra fp16 144 and 48; N = 37,
+// K = 1024, 3001 spectra fp16 190 and 166; N = 20, K = 512, 16384 spectra fp32
+// 427 and 338; nothing at N = 44, whose last line is needed.
+__device__ __forceinline__ int past_last(int N, int B, int lane) { return min(0, N - 1 - (16 * B + (lane & 15))); }
+
 // The accumulators of one wavefront's region: RB x RBJ pairs of 16-antenna
 // blocks (DIAG: the upper triangle of a square diagonal region) of one
 // channel, both
@@ -230,27 +238,33 @@ struct XRegion {
     // in flight while one is multiplied (2 where many waves share a SIMD and
     // hide each other's latency; more for a wave that runs alone).
     template <int NBUF = 2>
-    __device__ __forceinline__ void run(const uint4 *spec, int K, int a_pad, int f, int I0, int J0, int kb0,
+    __device__ __forceinline__ void run(const uint4 *spec, int K, int a_pad, int N, int f, int I0, int J0, int kb0,
                                         int kb1) {
         const int lane = threadIdx.x & 63;
         // lane (row r, group g) reads record tq = 4 kb + g of antenna 16 I + r;
         // a k-block is the (kb mod 4)-th quarter of time block kb / 4
         const uint4 *base = spec + (int64_t)f * kTQB * a_pad + (lane >> 4) * a_pad + (lane & 15);
         const int64_t bstride = (int64_t)K * kTQB * a_pad;
+        // the last block's padding antennas read the last antenna's record, so
+        // lines that hold padding alone stay unread (their products are not
+        // stored)
+        const uint4 *base_l = base + past_last(N, DIAG ? I0 + RB - 1 : J0 + RBJ - 1, lane);
 
         // two register sets alternate: the records of the next step are in
         // flight while the current one's are multiplied (below, k-block stands
         // for a step: kb0, kb1 and kb count steps of KB k-blocks)
         const float m1 = opaque_m1();
         auto load = [&](int kb, uint4 (&r)[RB][KB], uint4 (&c)[RBJ][KB]) {
-            const uint4 *rec = base + (kb >> (KB == 2 ? 1 : 2)) * bstride + (kb & (KB == 2 ? 1 : 3)) * 4 * KB * a_pad;
+            const int64_t at = (kb >> (KB == 2 ? 1 : 2)) * bstride + (kb & (KB == 2 ? 1 : 3)) * 4 * KB * a_pad;
+            const uint4 *rec = base + at, *rec_l = base_l + at;
 #pragma unroll
             for (int q = 0; q < KB; ++q) {
 #pragma unroll
-                for (int I = 0; I < RB; ++I) r[I][q] = rec[q * 4 * a_pad + (I0 + I) * 16];
+                for (int I = 0; I < RB; ++I)
+                    r[I][q] = (DIAG && I == RB - 1 ? rec_l : rec)[q * 4 * a_pad + (I0 + I) * 16];
                 if constexpr (!DIAG) {
 #pragma unroll
-                    for (int J = 0; J < RBJ; ++J) c[J][q] = rec[q * 4 * a_pad + (J0 + J) * 16];
+                    for (int J = 0; J < RBJ; ++J) c[J][q] = (J == RBJ - 1 ? rec_l : rec)[q * 4 * a_pad + (J0 + J) * 16];
                 }
             }
         };
@@ -425,7 +439,7 @@ __device__ __forceinline__ void x_wave(const XArgs &a, int wave, float *tb) {
     const int kb1 = (int)((int64_t)(sp + 1) * nst / a.nsplit);
     XRegion<PREC, RB, DIAG> x;
     x.zero();
-    x.run(a.spec, a.K, a.a_pad, f, I0, J0, kb0, kb1);
+    x.run(a.spec, a.K, a.a_pad, a.N, f, I0, J0, kb0, kb1);
     x.store(a.partial, ((int64_t)sp * a.K + f) * a.nb, a.N, I0, J0, tb);
 }
 
@@ -950,6 +964,7 @@ __device__ __forceinline__ void x_wave16(const XArgs &a, int wave) {
     // lane (row r, group g): records tq = 8 step + 2 g and + 1 of antenna 16 I + r
     const uint4 *base = a.spec + (int64_t)f * kTQB * a.a_pad + (2 * (lane >> 4)) * a.a_pad + (lane & 15);
     const int64_t bstride = (int64_t)a.K * kTQB * a.a_pad;
+    const int last = past_last(a.N, (DIAG ? I0 : J0) + RB - 1, lane);  // as in XRegion::run
     auto mm = [](i32x4 &acc, uint4 x, uint4 y) {
         const i32x4 av = {(int)x.x, (int)x.y, (int)x.z, (int)x.w};
         const i32x4 bv = {(int)y.x, (int)y.y, (int)y.z, (int)y.w};
@@ -961,7 +976,8 @@ __device__ __forceinline__ void x_wave16(const XArgs &a, int wave) {
         uint4 ph[RB], pl[RB], qh[RB], ql[RB], ch[RB], cl[RB];
 #pragma unroll
         for (int I = 0; I < RB; ++I) {
-            const uint4 r0 = rec[(I0 + I) * 16], r1 = rec[(I0 + I) * 16 + a.a_pad];
+            const uint4 *p = rec + (I0 + I) * 16 + (DIAG && I == RB - 1 ? last : 0);
+            const uint4 r0 = p[0], r1 = p[a.a_pad];
             ph[I] = make_uint4(r0.x, r0.y, r1.x, r1.y);
             pl[I] = make_uint4(r0.z, r0.w, r1.z, r1.w);
             qh[I] = make_uint4(r0.y, neg_i8x4(r0.x), r1.y, neg_i8x4(r1.x));
@@ -970,7 +986,8 @@ __device__ __forceinline__ void x_wave16(const XArgs &a, int wave) {
         if constexpr (!DIAG) {
 #pragma unroll
             for (int J = 0; J < RB; ++J) {
-                const uint4 r0 = rec[(J0 + J) * 16], r1 = rec[(J0 + J) * 16 + a.a_pad];
+                const uint4 *p = rec + (J0 + J) * 16 + (J == RB - 1 ? last : 0);
+                const uint4 r0 = p[0], r1 = p[a.a_pad];
                 ch[J] = make_uint4(r0.x, r0.y, r1.x, r1.y);
                 cl[J] = make_uint4(r0.z, r0.w, r1.z, r1.w);
             }
