@@ -40,6 +40,7 @@ def log(msg):
 
 
 KERNEL_SOURCES = {"fstage_kernel": ("fstage_dev.h", "fstage.hip", "corr_internal.h"),
+                  "fstage_reg_kernel": ("fstage_reg_dev.h", "fstage_dev.h", "fstage.hip", "corr_internal.h"),
                   "xstage_kernel": ("xstage_dev.h", "xstage.hip", "corr_internal.h")}
 
 
@@ -96,7 +97,8 @@ def f_stage_bounds(metrics, name, f_ms, group):
     out = {"hbm": {"achieved_gbs": round(gbs, 1), "frac": round(gbs / PEAK["hbm_gbs"], 4),
                    "bytes_per_antenna_sample": 0.5 + rec}}
     prec_code = {"fp32": 0, "fp16": 1, "int8": 2, "int16": 3}[name]
-    per_as = counted_valu(f"fstage_kernel<256, {prec_code}, {group}, false>")
+    kernel = f"fstage_kernel<256, 0, {group}, false>" if name == "fp32" else f"fstage_reg_kernel<256, {prec_code}, false>"
+    per_as = counted_valu(kernel)
     if per_as is not None:
         rate = per_as * a_s / (f_ms * 1e-3)
         out["alu"] = {"valu_lane_ops_per_antenna_sample": per_as, "achieved_lane_ops_per_s": float("%.4g" % rate),
@@ -388,12 +390,16 @@ def batch_fresh_process(steps, warmup):
 def x_mfma(metrics, N, K, S, prec, x_ms):
     """The X-stage's issued MFMA rate against the dense peak of its form
     (issued operations from the block-pair count; rocprofv3's
-    SQ_INSTS_VALU_MFMA_MOPS counters give the same totals)."""
+    SQ_INSTS_VALU_MFMA_MOPS counters give the same totals).  fp32 above 16
+    antennas issues three f16 products for each of its own, the float records
+    split in halves."""
     if x_ms <= 0:
         return None
-    rate = metrics.x_mfma_ops(N, K, S, prec) / (x_ms * 1e-3) / 1e12
+    halves = prec == "fp32" and N > 16
+    issued = 3 * metrics.x_mfma_ops(N, K, S, "fp16") if halves else metrics.x_mfma_ops(N, K, S, prec)
+    rate = issued / (x_ms * 1e-3) / 1e12
     useful = metrics.x_ops(N, K, S) / (x_ms * 1e-3) / 1e12
-    peak = metrics.MFMA_PEAK[prec]
+    peak = metrics.MFMA_PEAK["fp16" if halves else prec]
     return {"issued": round(rate, 2), "peak": peak, "unit": "TFLOP/s" if prec.startswith("fp") else "TOPS",
             "frac": round(rate / peak, 4), "useful": round(useful, 2), "useful_frac": round(useful / peak, 4)}
 
@@ -568,13 +574,13 @@ def main():
                 "traffic": None, "per_launch": {"useful_flops": flops, "avg_ms": st["fused"]}}
     elif st["x"] >= st["f"]:
         per_launch_ms = st["x"] / max(1, launches["x"])
-        flops = metrics.x_ops(N_ANT, K, chunk)
-        achieved = flops / (per_launch_ms * 1e-3) / 1e12
-        t = measured_traffic("xstage_kernel<0, 3, 1>", chunk)
-        roof = {"kernel": "xstage_kernel (fp32 MFMA, Hermitian rank-T update)", "bound": "mfma",
-                "achieved": round(achieved, 2), "peak": PEAK["fp32_tflops"], "unit": "TFLOP/s",
-                "frac": round(achieved / PEAK["fp32_tflops"], 4), "traffic": t,
-                "per_launch": {"useful_flops": flops, "avg_ms": round(per_launch_ms, 4)}}
+        nbytes = metrics.padded_antennas(N_ANT) * K * chunk * 8.0
+        achieved = nbytes / (per_launch_ms * 1e-3) / 1e9
+        t = measured_traffic("xstage_kernel<4, 3, 1>", chunk)
+        roof = {"kernel": "xstage_kernel (float records as f16 halves, Hermitian rank-T update)", "bound": "hbm",
+                "achieved": round(achieved, 1), "peak": PEAK["hbm_gbs"], "unit": "GB/s",
+                "frac": round(achieved / PEAK["hbm_gbs"], 4), "traffic": t,
+                "per_launch": {"algorithmic_bytes": nbytes, "avg_ms": round(per_launch_ms, 4)}}
     else:
         per_launch_ms = st["f"] / max(1, launches["f"])
         nbytes = metrics.antenna_samples(N_ANT, TWO_K, chunk) * (0.5 + 4.0)

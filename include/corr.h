@@ -91,7 +91,9 @@ int corr_set_precision(corr_handle h, int mode);
  *   chunk_spectra: spectra per F->X chunk (multiple of 64).
  *   x_splits:      time splits of one chunk in the X-stage (partials per
  *                  channel per chunk; 1..64).
- *   f_group:       antennas per F-stage tile (2, 4 or 8).
+ *   f_group:       antennas per F-stage tile (1, 2, 4, 8 or 16; without effect on FP16,
+ *                  INT8 and INT16 records of 256 and 512 channels, whose units are
+ *                  of one size).
  * Allowed only before the first process call, else CORR_ESTATE.  */
 typedef struct {
     int chunk_spectra;
@@ -115,7 +117,9 @@ int corr_get_tiles(corr_handle h, corr_tiles *t);
  *     out once (float forms: every 2048 (FP32) / 16384 (FP16) spectra of a
  *     partial); one dump follows.  Two layouts of the roles:
  *       mixed (f_cus_per_xcd = 0): every CU runs f_workgroups_per_cu F
- *         workgroups and its other resident workgroups run X;
+ *         workgroups and its other resident workgroups run X (FP16 and INT8 at
+ *         256 and 512 channels keep two workgroups resident; their layouts are
+ *         accepted as for three and cut to what two can run);
  *       split (f_cus_per_xcd > 0): the first f_cus_per_xcd CUs of each XCD
  *         run only F workgroups and the other CUs only X workgroups
  *         (f_workgroups_per_cu must then be 0; at most CUs per XCD - 1).

@@ -18,6 +18,8 @@
 // of GA consecutive antennas; its outputs are staged in LDS and written as
 // 16-byte records [re x TS][im x TS], GA records (GA*16 bytes) contiguous
 // per channel.  Power mode sums |X|^2 over the calibration window instead.
+// fp16, int8 and int16 records of 256 and 512 channels are made by the register
+// transform of fstage_reg_dev.h instead.
 #pragma once
 #include <type_traits>
 #include "corr_internal.h"
