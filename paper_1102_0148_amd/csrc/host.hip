@@ -624,18 +624,21 @@ int launch_x_and_dump(corr_ctx *h, const uint4 *spec, int ntq, int nkb, bool own
         xa.groups = h->xgroups;
         xa.ngroups = h->n_xgroups;
         HIP_TRY(launch_xgroups(xprec, xa, st), "X-stage launch");
-    } else if (h->n_off && h->prec != kFP32) {
+    } else if (h->n_off && (h->prec != kFP32 || xprec == kFP32H)) {
         // one launch over every region of a channel (diagonal ones first), so
         // the regions that share records read them from HBM once, through one
         // L2: the int8, fp16 and int16 forms are bound by that traffic (int16,
         // two launches and one: N = 61, K = 512, 5001 spectra 378 and 200 us;
         // N = 256, K = 256, 4096 spectra 747 and 549 us; N = 75, whose regions
-        // are single blocks, 248 and 174 us)
+        // are single blocks, 248 and 174 us), and fp32 as halves is not far
+        // from it (N = 100, K = 256, 8192 spectra 800 and 667 us; N = 192,
+        // K = 512, 4096 spectra 1527 and 1192 us; N = 128, K = 256, 512 spectra
+        // 73 and 62 us)
         xa.nregions = h->n_diag + h->n_off;
         HIP_TRY(launch_xstage(xprec, h->rb, 2, xa, st), "X-stage launch");
     } else {
-        // fp32 is bound by MFMA rate, and its diagonal regions keep more waves
-        // per SIMD in a launch of their own
+        // fp32's own products are bound by MFMA rate, and its diagonal regions
+        // keep more waves per SIMD in a launch of their own
         xa.nregions = h->n_diag;
         HIP_TRY(launch_xstage(xprec, h->rb, 1, xa, st), "X-stage launch");
         if (h->n_off) {
