@@ -279,6 +279,7 @@ struct corr_ctx {
     int2 *regions = nullptr;
     unsigned long long *sat = nullptr;
     unsigned *fticket = nullptr;  // F-stage tile-chunk counters
+    bool tickets_used = false;    // an F-stage was enqueued and the dump that clears its tickets was not
     // a job of a branches-mode batch: its input pointer, which the kernels
     // read from this device slot when the graph replays
     const uint8_t *const *in_slot = nullptr;
@@ -653,6 +654,7 @@ int launch_x_and_dump(corr_ctx *h, const uint4 *spec, int ntq, int nkb, bool own
     HIP_TRY(launch_dump(h->prec, h->partial, h->acc, h->tiles.x_splits, h->K, h->nb, h->fresh, h->fticket, st),
             "dump launch");
     h->fresh = false;
+    h->tickets_used = false;
     timer_end(h, st);
     return CORR_OK;
 }
@@ -748,6 +750,9 @@ int process_one(corr_ctx *h, const uint8_t *in, hipStream_t st) {
         h->dbg_spec = h->spec + (int64_t)(last % h->fx_ring) * h->fx_slot_recs;
         return CORR_OK;
     }
+    // what an earlier call that failed between its F-stage and its dump left:
+    // with used tickets this F-stage would write nothing
+    if (h->tickets_used) HIP_TRY(launch_fill_zero(h->fticket, kTicketBytes, st), "ticket clear");
     for (int c0 = 0; c0 < h->S; c0 += chunk) {
         const int Sc = std::min(chunk, h->S - c0);
         const int ntq_used = round_up((Sc + h->TG - 1) / h->TG, step_records(h->prec));
@@ -771,6 +776,7 @@ int process_one(corr_ctx *h, const uint8_t *in, hipStream_t st) {
         fa.ngroups = ngroups;
         fa.ntiles = ntq_used * ngroups;
         timer_begin(h, 1, st);
+        h->tickets_used = true;
         HIP_TRY(launch_fstage(h->K, h->prec, ga, 0, fa, 0, st), "F-stage launch");
         timer_end(h, st);
         h->launches_f++;
