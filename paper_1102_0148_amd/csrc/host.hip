@@ -451,11 +451,13 @@ int plan_fused(corr_ctx *h) {
     if (!chunk) chunk = (int)std::max<int64_t>(64, ((int64_t)72 << 20) / per_spectrum / 64 * 64);
     chunk = (int)std::min<int64_t>(chunk, round_up64(h->S, 64));
     // a partial sums at most 2048 (fp32) / 16384 (fp16) spectra; int8 sums
-    // are exact over the whole integration
+    // are exact over the whole integration.  The X units of a channel share a
+    // chunk out in whole steps, and some get the larger share of every chunk.
     const int cap = h->prec == kFP32 ? kF32SplitSpectra : h->prec == kFP16 ? kF16SplitSpectra : 0;
+    const int step = step_records(h->prec) * h->TG;
     const auto unit_spectra = [&](int nsplit) {
-        const int kb_chunk = (chunk + 4 * h->TG - 1) / (4 * h->TG);
-        return (kb_chunk + nsplit - 1) / nsplit * 4 * h->TG;
+        const int steps = (chunk + step - 1) / step;
+        return (steps + nsplit - 1) / nsplit * step;
     };
     if (cap && unit_spectra(arg_nsplit) > cap)
         return fail(CORR_EINVAL, "chunk_spectra=%d gives %d spectra per partial in one chunk, above %d", chunk,
