@@ -284,10 +284,11 @@ constexpr int kFxXBuf = 4;
 // Largest region side (in 16-antenna blocks) the fused kernel is built for.
 constexpr int kFxMaxRB = 3;
 // The chunk's spin limit is the batch kernel's (about a second).
-hipError_t launch_fused(int M, int prec, int rb, const FxArgs &a, int grid, hipStream_t st);
+// xprec: the precision, or kFP32H for fp32 with its products as halves.
+hipError_t launch_fused(int M, int xprec, int rb, const FxArgs &a, int grid, hipStream_t st);
 // Workgroups of the fused kernel that stay resident per CU (0 if the
 // combination is not built), and its F group.
-int fused_blocks_per_cu(int M, int prec, int rb);
+int fused_blocks_per_cu(int M, int xprec, int rb);
 int fused_group(int M, int prec);
 
 // ---------------------------------------------------------------- dump etc.

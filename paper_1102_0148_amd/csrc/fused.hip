@@ -122,14 +122,13 @@ __device__ __forceinline__ void fx_f_role(const FxArgs &a, float2 *zbuf, uint32_
     }
 }
 
-template <int PREC, int RB>
+template <int XP, int RB>
 __device__ __forceinline__ void fx_x_role(const FxArgs &a, int xrank, float *tb) {
-    const int tg = record_times(PREC);
+    const int tg = record_times(XP);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int unit = xrank * 4 + w;
     const bool active = unit < a.x.K * a.x.nsplit;
     const int f = unit % a.x.K, sp = unit / a.x.K;
-    constexpr int XP = PREC == kFP32 ? kFP32H : PREC;
     typedef XRegion<XP, RB, true> Region;
     Region acc;
     acc.zero();
@@ -168,7 +167,8 @@ __device__ __forceinline__ void fx_x_role(const FxArgs &a, int xrank, float *tb)
 // two, and so do the register transforms.
 constexpr int fx_min_blocks(int M, int prec) { return M <= 256 && !uses_reg_fft(M, prec) ? 3 : 2; }
 
-template <int M, int PREC, int GA, int RB>
+// XP: the products' form (kFP32 or kFP32H for fp32, else PREC).
+template <int M, int PREC, int GA, int RB, int XP>
 __global__ __launch_bounds__(kThreads, fx_min_blocks(M, PREC)) void fx_kernel(FxArgs kargs) {
     using Sh = FShape<M, PREC, GA, false>;
     static_assert(Sh::LDS <= 160 * 1024, "LDS budget");
@@ -194,54 +194,58 @@ __global__ __launch_bounds__(kThreads, fx_min_blocks(M, PREC)) void fx_kernel(Fx
         fx_f_role<M, PREC, GA>(a, zbuf, bbuf, s_tk, ops);
     } else {
         float *tb = reinterpret_cast<float *>(zbuf) + (threadIdx.x >> 6) * 16 * 17;
-        fx_x_role<PREC, RB>(a, xrank, tb);
+        fx_x_role<XP, RB>(a, xrank, tb);
     }
 }
 
-template <int M, int PREC, int RB>
+template <int M, int XP, int RB>
+constexpr auto fx_instance() {
+    constexpr int PREC = XP == kFP32H ? kFP32 : XP;
+    return fx_kernel<M, PREC, fx_group(M, PREC), RB, XP>;
+}
+
+template <int M, int XP, int RB>
 hipError_t launch_fx(const FxArgs &a, int grid, hipStream_t st) {
-    constexpr int GA = fx_group(M, PREC);
     void *args[] = {const_cast<FxArgs *>(&a)};
-    hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(fx_kernel<M, PREC, GA, RB>),
-                                              dim3(grid), dim3(kThreads), args, 0, st);
+    hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(fx_instance<M, XP, RB>()), dim3(grid),
+                                              dim3(kThreads), args, 0, st);
     if (e != hipSuccess) return e;
     return hipGetLastError();
 }
 
-template <int M, int PREC, int RB>
+template <int M, int XP, int RB>
 int fx_per_cu() {
-    constexpr int GA = fx_group(M, PREC);
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fx_kernel<M, PREC, GA, RB>, kThreads, 0) !=
-        hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fx_instance<M, XP, RB>(), kThreads, 0) != hipSuccess)
         return 0;
     return per_cu;
 }
 
-template <int M, int PREC>
+template <int M, int XP>
 hipError_t launch_fx_mp(int rb, const FxArgs &a, int grid, hipStream_t st) {
     switch (rb) {
-        case 1: return launch_fx<M, PREC, 1>(a, grid, st);
-        case 2: return launch_fx<M, PREC, 2>(a, grid, st);
-        case 3: return launch_fx<M, PREC, 3>(a, grid, st);
+        case 1: return launch_fx<M, XP, 1>(a, grid, st);
+        case 2: return launch_fx<M, XP, 2>(a, grid, st);
+        case 3: return launch_fx<M, XP, 3>(a, grid, st);
     }
     return hipErrorInvalidValue;
 }
 
-template <int M, int PREC>
+template <int M, int XP>
 int per_cu_mp(int rb) {
     switch (rb) {
-        case 1: return fx_per_cu<M, PREC, 1>();
-        case 2: return fx_per_cu<M, PREC, 2>();
-        case 3: return fx_per_cu<M, PREC, 3>();
+        case 1: return fx_per_cu<M, XP, 1>();
+        case 2: return fx_per_cu<M, XP, 2>();
+        case 3: return fx_per_cu<M, XP, 3>();
     }
     return 0;
 }
 
 template <int M>
-hipError_t launch_fx_m(int prec, int rb, const FxArgs &a, int grid, hipStream_t st) {
-    switch (prec) {
+hipError_t launch_fx_m(int xprec, int rb, const FxArgs &a, int grid, hipStream_t st) {
+    switch (xprec) {
         case kFP32: return launch_fx_mp<M, kFP32>(rb, a, grid, st);
+        case kFP32H: return launch_fx_mp<M, kFP32H>(rb, a, grid, st);
         case kFP16: return launch_fx_mp<M, kFP16>(rb, a, grid, st);
         case kINT8: return launch_fx_mp<M, kINT8>(rb, a, grid, st);
     }
@@ -249,9 +253,10 @@ hipError_t launch_fx_m(int prec, int rb, const FxArgs &a, int grid, hipStream_t 
 }
 
 template <int M>
-int per_cu_m(int prec, int rb) {
-    switch (prec) {
+int per_cu_m(int xprec, int rb) {
+    switch (xprec) {
         case kFP32: return per_cu_mp<M, kFP32>(rb);
+        case kFP32H: return per_cu_mp<M, kFP32H>(rb);
         case kFP16: return per_cu_mp<M, kFP16>(rb);
         case kINT8: return per_cu_mp<M, kINT8>(rb);
     }
@@ -262,23 +267,23 @@ int per_cu_m(int prec, int rb) {
 
 int fused_group(int M, int prec) { return fx_group(M, prec); }
 
-int fused_blocks_per_cu(int M, int prec, int rb) {
+int fused_blocks_per_cu(int M, int xprec, int rb) {
     if (rb < 1 || rb > kFxMaxRB) return 0;
     switch (M) {
-        case 128: return per_cu_m<128>(prec, rb);
-        case 256: return per_cu_m<256>(prec, rb);
-        case 512: return per_cu_m<512>(prec, rb);
-        case 1024: return per_cu_m<1024>(prec, rb);
+        case 128: return per_cu_m<128>(xprec, rb);
+        case 256: return per_cu_m<256>(xprec, rb);
+        case 512: return per_cu_m<512>(xprec, rb);
+        case 1024: return per_cu_m<1024>(xprec, rb);
     }
     return 0;
 }
 
-hipError_t launch_fused(int M, int prec, int rb, const FxArgs &a, int grid, hipStream_t st) {
+hipError_t launch_fused(int M, int xprec, int rb, const FxArgs &a, int grid, hipStream_t st) {
     switch (M) {
-        case 128: return launch_fx_m<128>(prec, rb, a, grid, st);
-        case 256: return launch_fx_m<256>(prec, rb, a, grid, st);
-        case 512: return launch_fx_m<512>(prec, rb, a, grid, st);
-        case 1024: return launch_fx_m<1024>(prec, rb, a, grid, st);
+        case 128: return launch_fx_m<128>(xprec, rb, a, grid, st);
+        case 256: return launch_fx_m<256>(xprec, rb, a, grid, st);
+        case 512: return launch_fx_m<512>(xprec, rb, a, grid, st);
+        case 1024: return launch_fx_m<1024>(xprec, rb, a, grid, st);
     }
     return hipErrorInvalidValue;
 }

@@ -302,6 +302,7 @@ struct corr_ctx {
     // sticky error flag
     int pipeline = CORR_PIPELINE_STAGED;
     int fx_chunk = 0, fx_ring = 0, fx_fpc = 0, fx_fcus = 0, fx_cus = 0;
+    int fx_xprec = kFP32;  // form of the products
     int fx_grid = 0, fx_nfwg = 0, fx_nsplit = 0, fx_flush = 0, fx_nchunks = 0, fx_nslots = 0;
     int64_t fx_slot_recs = 0;
     unsigned *fx_ctr = nullptr;
@@ -403,6 +404,12 @@ int default_splits(const corr_ctx *h) { return splits_for(n_regions(h), h->K, h-
 
 hipError_t set_regions(corr_ctx *h, int rb);
 
+// Whether partials of nkb k-blocks over nsplit splits hold enough spectra for the
+// products as halves: in few, the f32 products round no more often than the halves
+// (against float64, N = 24, 64 spectra in 16 splits: 9.3e-8, halves 9.6e-8; 37 spectra a
+// split, N = 44: 9.7e-8, halves 8.9e-8).
+bool enough_for_halves(int nkb, int nsplit) { return nkb * 8 >= nsplit * 32; }
+
 // Resolve tiles and allocate the precision-dependent scratch.
 // The fused pipeline's plan: roles, splits, chunks, ring and partials.
 int plan_fused(corr_ctx *h) {
@@ -411,14 +418,13 @@ int plan_fused(corr_ctx *h) {
     if (h->n_diag != 1 || h->n_off != 0 || h->rb > kFxMaxRB)
         return fail(CORR_EINVAL, "the fused pipeline covers N <= %d (one region of at most %d antenna blocks), got N=%d",
                     16 * kFxMaxRB, kFxMaxRB, h->N);
-    const int per_cu = fused_blocks_per_cu(h->K, h->prec, h->rb);
+    int per_cu = fused_blocks_per_cu(h->K, h->prec, h->rb);
     int cus = 0;
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device), "hipDeviceGetAttribute");
     if (per_cu < 2 || cus < 1) return fail(CORR_EINVAL, "the fused kernel keeps %d workgroups per CU resident; it needs 2", per_cu);
     // workgroup b runs on XCD b mod 8 (gfx950: 8 XCDs of 32 CUs), and each
     // XCD's F workgroups publish through that XCD's L2
     if (cus % 8) return fail(CORR_EINVAL, "the fused pipeline expects the CUs in 8 XCDs (%d CUs)", cus);
-    h->fx_grid = per_cu * cus;
     h->fx_cus = cus;
     // The register transform's kernels keep two workgroups per CU (72 KB of
     // operands and 256 registers), the other forms' three or more.  Their
@@ -436,6 +442,21 @@ int plan_fused(corr_ctx *h) {
     if (h->K > arg_waves)
         return fail(CORR_EINVAL, "the fused pipeline needs %d X waves for K=%d, has %d", h->K, h->K, arg_waves);
     const int arg_nsplit = std::max(1, std::min(64, arg_waves / h->K));
+    // fp32: the products as halves, but in partials of a few spectra, and where three workgroups share a CU and two or three
+    // antenna blocks leave the halves' kernel short of registers: there only in
+    // the layouts that X bounds.  S = 16384, f32 products and halves (us), N = 44,
+    // K = 128 with two F workgroups a CU 380 and 427, one 468 and 393, 24 CUs an
+    // XCD on F 667 and 411; N = 32, K = 128 with 8 and 16 such CUs 417 and 436, 291
+    // and 303, with 20 316 and 266; N = 48, K = 256, 736 and 773, 891 and 735, 1267
+    // and 760.  Two workgroups a CU (N = 44, K = 512) 1634 and 1274; one block (N = 12,
+    // K = 256) 302 and 294.
+    const bool x_bound = fcus ? 16 * fcus > cus : fpc == 1;
+    const int nkb = round_up((h->S + h->TG - 1) / h->TG, step_records(h->prec)) / 4;
+    const bool halves = h->prec == kFP32 && enough_for_halves(nkb, arg_nsplit) && (per_cu < 3 || h->rb == 1 || x_bound);
+    h->fx_xprec = halves ? kFP32H : h->prec;
+    if (halves) per_cu = fused_blocks_per_cu(h->K, kFP32H, h->rb);
+    if (per_cu < 2) return fail(CORR_EINVAL, "the fused kernel keeps %d workgroups per CU resident; it needs 2", per_cu);
+    h->fx_grid = per_cu * cus;
     fpc = std::min(fpc, per_cu - 1);
     while (fcus > 1 && h->K > waves(per_cu)) --fcus;
     const int x_waves = waves(per_cu);
@@ -454,7 +475,7 @@ int plan_fused(corr_ctx *h) {
     // are exact over the whole integration.  The X units of a channel share a
     // chunk out in whole steps, and some get the larger share of every chunk.
     const int cap = h->prec == kFP32 ? kF32SplitSpectra : h->prec == kFP16 ? kF16SplitSpectra : 0;
-    const int step = step_records(h->prec) * h->TG;
+    const int step = h->fx_xprec == kFP32 ? kblock_times(kFP32) : step_records(h->prec) * h->TG;
     const auto unit_spectra = [&](int nsplit) {
         const int steps = (chunk + step - 1) / step;
         return (steps + nsplit - 1) / nsplit * step;
@@ -596,11 +617,9 @@ int timers_collect(corr_ctx *h) {
 int launch_x_and_dump(corr_ctx *h, const uint4 *spec, int ntq, int nkb, bool own, hipStream_t st) {
     // Float records as halves but where that gains nothing: one block of antennas
     // streams its records as fast through the f32 products (N = 16, K = 512, 16384
-    // spectra: 176 us, 168 as halves), and in partials of a few spectra, where the
-    // launch is latency, the f32 products round no more often than the halves
-    // (against float64, N = 24, 64 spectra in 16 splits: 9.3e-8, halves 9.6e-8;
-    // 37 spectra a split, N = 44: 9.7e-8, halves 8.9e-8).
-    const bool halves = own && h->nblk > 1 && nkb * 8 >= h->tiles.x_splits * 32;
+    // spectra: 176 us, 168 as halves), and partials of a few spectra, whose launch
+    // is latency.
+    const bool halves = own && h->nblk > 1 && enough_for_halves(nkb, h->tiles.x_splits);
     const int xprec = h->prec == kFP32 && halves ? kFP32H : h->prec;
     XArgs xa{};
     xa.spec = spec;
@@ -741,7 +760,7 @@ int process_one(corr_ctx *h, const uint8_t *in, hipStream_t st) {
         fx.flush_chunks = h->fx_flush;
         HIP_TRY(launch_fill_zero(h->fx_ctr, h->fx_ctr_bytes, st), "fused counter clear");
         timer_begin(h, 4, st);
-        HIP_TRY(launch_fused(h->K, h->prec, h->rb, fx, h->fx_grid, st), "fused F + X launch");
+        HIP_TRY(launch_fused(h->K, h->fx_xprec, h->rb, fx, h->fx_grid, st), "fused F + X launch");
         timer_end(h, st);
         h->launches_fused++;
         timer_begin(h, 3, st);

@@ -1,4 +1,5 @@
 """The fused pipeline's partials: how many spectra one of them sums."""
+import numpy as np
 import pytest
 
 import oracle
@@ -30,3 +31,19 @@ def test_fp32_partials_sum_at_most_2048_spectra(K, chunks, chunk, f_cus):
     err = coef_error(raw_to_complex(c.read_cps_raw()), oracle.correlate(packed.numpy(), S, N, K), N)
     assert err <= TOL[corr.CORR_FP32]
     c.close()
+
+
+# partials of under 32 spectra: products of the staged pipeline's form, the same sums to the bit
+# (one k-block of 8 spectra, three, and all of a channel's to a unit)
+@pytest.mark.parametrize("N,K,S", [(8, 128, 64), (17, 128, 64), (44, 128, 64), (33, 512, 48), (20, 1024, 24)])
+def test_fp32_short_partials_are_the_staged_ones(N, K, S):
+    x = synth.packed(synth.recipe_plain(N=N, two_k=2 * K, rho=0.3, seed=N), 0, S).contiguous().cuda()
+    c = corr.Correlator(N, K, S, pipeline="fused")
+    splits = c.tiles()["x_splits"]
+    assert S < 32 * splits
+    s = corr.Correlator(N, K, S, tiles=dict(x_splits=splits))
+    c.process(x)
+    s.process(x)
+    np.testing.assert_array_equal(c.read_cps_raw(), s.read_cps_raw())
+    c.close()
+    s.close()
