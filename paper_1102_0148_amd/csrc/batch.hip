@@ -174,8 +174,9 @@ __global__ __launch_bounds__(256, 2) void batch_kernel(const BJob *jobs, const u
                 const XArgs &xa = diag ? j.xd : j.xo;
                 float *tb = reinterpret_cast<float *>(lds) + w * 16 * 17;
                 const int wave = it.a0 * 4 + w;
-                switch (j.prec) {
-                    case kFP32: x_dispatch<kFP32H>(xa, diag ? j.rb_d : j.rb_o, diag, wave, tb); break;
+                switch (j.xprec) {
+                    case kFP32: x_dispatch<kFP32>(xa, diag ? j.rb_d : j.rb_o, diag, wave, tb); break;
+                    case kFP32H: x_dispatch<kFP32H>(xa, diag ? j.rb_d : j.rb_o, diag, wave, tb); break;
                     case kFP16: x_dispatch<kFP16>(xa, diag ? j.rb_d : j.rb_o, diag, wave, tb); break;
                     default: x_dispatch<kINT8>(xa, diag ? j.rb_d : j.rb_o, diag, wave, tb); break;
                 }

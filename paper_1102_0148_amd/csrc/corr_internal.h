@@ -335,6 +335,7 @@ struct BJob {
     double2 *acc;        // integration buffer [K][nb]
     float *scales, *scales_p;
     int K, prec, rb_d, rb_o;
+    int xprec;           // the X-stage's form (kFP32H: float records as halves)
     int n_acc;           // K * nb
     int W, nparts;       // calibration window and power partials
     int sc_n;            // N * K scale entries

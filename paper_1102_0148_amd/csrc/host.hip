@@ -612,15 +612,19 @@ int timers_collect(corr_ctx *h) {
     return CORR_OK;
 }
 
+// The form of the products of a chunk of nkb k-blocks of the F-stage's own records:
+// float records as halves but where that gains nothing: one block of antennas
+// streams its records as fast through the f32 products (N = 16, K = 512, 16384
+// spectra: 176 us, 168 as halves), and partials of a few spectra, whose launch
+// is latency.
+int own_xprec(const corr_ctx *h, int nkb) {
+    return h->prec == kFP32 && h->nblk > 1 && enough_for_halves(nkb, h->tiles.x_splits) ? kFP32H : h->prec;
+}
+
 // `own`: the records are the F-stage's (padded to whole steps, components at
 // most 16384); false: a caller's.
 int launch_x_and_dump(corr_ctx *h, const uint4 *spec, int ntq, int nkb, bool own, hipStream_t st) {
-    // Float records as halves but where that gains nothing: one block of antennas
-    // streams its records as fast through the f32 products (N = 16, K = 512, 16384
-    // spectra: 176 us, 168 as halves), and partials of a few spectra, whose launch
-    // is latency.
-    const bool halves = own && h->nblk > 1 && enough_for_halves(nkb, h->tiles.x_splits);
-    const int xprec = h->prec == kFP32 && halves ? kFP32H : h->prec;
+    const int xprec = own ? own_xprec(h, nkb) : h->prec;
     XArgs xa{};
     xa.spec = spec;
     xa.partial = h->partial;
@@ -1482,6 +1486,7 @@ int batch_build(corr_ctx *b) {
         d.scales_p = h->scales_p;
         d.K = h->K;
         d.prec = h->prec;
+        d.xprec = own_xprec(h, xa.nkb);
         d.rb_d = rb;
         d.rb_o = rb;
         d.n_acc = h->K * h->nb;
