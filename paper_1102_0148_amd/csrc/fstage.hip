@@ -62,14 +62,27 @@ __global__ __launch_bounds__(kThreads, 2) void fstage_reg_kernel(FArgs kargs) {
     if (args.in_slot)
         args.in = (const uint8_t *)*reinterpret_cast<const gptr *>(args.in_slot) + (int64_t)args.s_base * args.N * M;
     __shared__ __attribute__((aligned(16))) uint4 lds[kRegLds];
-    reg_load_ops<M>(args, lds);
-    __syncthreads();
     __shared__ int s_tk[2];
     const int sets = args.ntiles / 4;  // a chunk has a multiple of 4 time records
     const int t8 = (sets + 7) / 8;
-    const int x = blockIdx.x % 8;
+    const int x = blockIdx.x % 8, rank = blockIdx.x / 8, wgs = gridDim.x / 8;
     const int lo = x * t8, hi = min(lo + t8, sets);
-    reg_units_dyn<M, PREC, TRACK>(args, lo, hi, args.ticket + kTicketStride * x, s_tk, lds);
+    // A workgroup's first two sets go by its rank on the XCD, so that their tickets,
+    // the samples and the operands are not fetched one after another.  Calls queued
+    // back to back, before and so (us; with the LDS transform of up to 16 sequences a
+    // workgroup, which this one replaced, in brackets): K = 256, N = 4, 444 spectra
+    // fp16 19.3 and 17.5 (25.0), int8 36.7 and 36.0 (37.1), int16 39.2 and 39.0 (37.5: 16
+    // sequences in one wavefront take longer than in four); K = 512, N = 16, 64 spectra
+    // int16 41.4 and 40.7 (40.4); N = 44, K = 256, 4096 spectra int8 117.4 and 114.6
+    // (141.9).  Few units keep this transform all the same: the codes of an
+    // integration do not depend on the chunks it is cut into.
+    const int set = lo + rank;
+    if (set >= hi) return;
+    u32x4 raw[4];
+    reg_load_set<M, PREC>(args, set, raw);
+    reg_load_ops<M>(args, lds);  // waits for the samples too
+    __syncthreads();
+    reg_sets<M, PREC, TRACK>(args, set, set + wgs, lo + 2 * wgs, hi, args.ticket + kTicketStride * x, s_tk, lds, raw);
 }
 
 template <int M, int PREC, bool TRACK>

@@ -567,27 +567,17 @@ __device__ __forceinline__ void reg_units(const FArgs &args, int u0, int u1, con
     reg_add_sat<PREC>(args, wsat);
 }
 
-// Sets [lo, hi) of four units dealt one per ticket by *ctr (zero at launch), as f_tiles_dyn
-// deals tiles: thread 0 holds a ticket ahead and publishes the next one in s_tk before
-// the barrier that ends a set.
+// Sets of four units, first `set`, whose bytes raw holds, then `next`, then base + ticket
+// for tickets of *ctr (zero at launch), below hi, as f_tiles_dyn deals tiles: thread 0
+// holds a ticket ahead and publishes the next one in s_tk before the barrier that ends a
+// set.
 template <int M, int PREC, bool TRACK>
-__device__ __forceinline__ void reg_units_dyn(const FArgs &args, int lo, int hi, unsigned *ctr, int *s_tk,
-                                              const uint4 *lds) {
+__device__ __forceinline__ void reg_sets(const FArgs &args, int set, int next, int base, int hi, unsigned *ctr, int *s_tk,
+                                         const uint4 *lds, u32x4 (&raw)[4]) {
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (tid == 0) {
-        s_tk[0] = (int)atomicAdd(ctr, 1u);
-        s_tk[1] = (int)atomicAdd(ctr, 1u);
-    }
-    __syncthreads();
-    int set = lo + s_tk[0], next = lo + s_tk[1];
-    __syncthreads();  // s_tk[0] is rewritten below
-    if (set >= hi) return;
     int tq, ga, tn, gn;
     reg_unit_at(4 * set + w, args.ngroups, tq, ga);
-    u32x4 raw[4];
-    reg_load<M, PREC>(args, tq, ga, raw);
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // as in f_tiles
     unsigned wsat = 0, tk = 0;
     for (;;) {
         if (tid == 0) tk = atomicInc(ctr, 0xffffffffu);
@@ -604,10 +594,36 @@ __device__ __forceinline__ void reg_units_dyn(const FArgs &args, int lo, int hi,
         set = next;
         tq = tn;
         ga = gn;
-        next = lo + s_tk[0];
+        next = base + s_tk[0];
         __syncthreads();  // s_tk has been read
     }
     reg_add_sat<PREC>(args, wsat);
+}
+
+// Load the bytes of this wavefront's unit of a set.
+template <int M, int PREC>
+__device__ __forceinline__ void reg_load_set(const FArgs &args, int set, u32x4 (&raw)[4]) {
+    int tq, ga;
+    reg_unit_at(4 * set + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), args.ngroups, tq, ga);
+    reg_load<M, PREC>(args, tq, ga, raw);
+}
+
+// Sets [lo, hi), every one by ticket.
+template <int M, int PREC, bool TRACK>
+__device__ __forceinline__ void reg_units_dyn(const FArgs &args, int lo, int hi, unsigned *ctr, int *s_tk,
+                                              const uint4 *lds) {
+    if (threadIdx.x == 0) {
+        s_tk[0] = (int)atomicAdd(ctr, 1u);
+        s_tk[1] = (int)atomicAdd(ctr, 1u);
+    }
+    __syncthreads();
+    const int set = lo + s_tk[0], next = lo + s_tk[1];
+    __syncthreads();  // s_tk[0] is rewritten below
+    if (set >= hi) return;
+    u32x4 raw[4];
+    reg_load_set<M, PREC>(args, set, raw);
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // as in f_tiles
+    reg_sets<M, PREC, TRACK>(args, set, next, lo, hi, ctr, s_tk, lds, raw);
 }
 
 }  // namespace
