@@ -56,7 +56,15 @@ enum corr_status {
     CORR_ESTATE = -4  /* call not allowed in the handle's current state */
 };
 
-/* Arithmetic of the X-stage.  FP32: float spectra, float products and sums.
+/* Arithmetic of the X-stage.  FP32: float spectra and float sums.  Spectra
+ * given to corr_process_spectra, those of up to 16 antennas (staged pipeline and
+ * batches) and partial sums of under 32 spectra are multiplied as floats; the
+ * fused pipeline multiplies as floats in some of its layouts.  Otherwise each
+ * component of the library's own spectra is multiplied as the sum of two
+ * half-precision numbers, within 2^-23 of its value (2^-25 where it is below
+ * 1/4), and the product of two lower halves, below 2^-22 of the components'
+ * product, is left out in imaginary parts and between antennas of different
+ * blocks of 16; the products add up in float.
  * FP16: spectra rounded to half (ties to even), float accumulation.  INT8:
  * spectra requantised per antenna and channel (Section 4's conversion to a
  * short integer type with prescaling, here to 8 bits), exact int32 sums.
