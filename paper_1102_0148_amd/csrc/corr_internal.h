@@ -230,8 +230,8 @@ struct XArgs {
     int ngroups;
 };
 // rb: region side in 16-antenna blocks; kind 1: regions on the diagonal
-// (upper-triangle pairs only), 0: off the diagonal (full rb x rb), 2: both,
-// the first a.n_diag regions diagonal (rb 2..4).
+// (upper-triangle pairs only), 0: off the diagonal (full rb x rb; kFP32, rb 4), 2:
+// both, the first a.n_diag regions diagonal (the other forms, rb 4; int16 rb 1, 2).
 hipError_t launch_xstage(int prec, int rb, int kind, const XArgs &a, hipStream_t st);
 // int8 / fp16 with 4 x 4-block regions: one workgroup per (group, channel,
 // split), the group's blocks staged through an LDS ring (a.groups).
@@ -239,8 +239,8 @@ hipError_t launch_xgroups(int prec, const XArgs &a, hipStream_t st);
 // int8 / fp16 with 4 x 4-block regions in exactly 4 region rows (16 blocks):
 // one workgroup per (channel, split) stages all 16 blocks of a k-block.
 hipError_t launch_xchan(int prec, const XArgs &a, hipStream_t st);
-// int16 (also reached through launch_xstage): rb <= 3 diagonal, rb <= 2 off
-// the diagonal; a.nkb even; partials are double2 (exact integers).
+// int16 (also reached through launch_xstage): rb <= 3 diagonal alone, rb <= 2
+// with both kinds; a.nkb even; partials are double2 (exact integers).
 hipError_t launch_xstage16(int rb, int kind, const XArgs &a, hipStream_t st);
 
 // ---------------------------------------------------------------- fused F -> X

@@ -49,29 +49,23 @@ hipError_t launch_one(const XArgs &a, hipStream_t st) {
     return hipGetLastError();
 }
 
+// Channels of more than one region have regions of 4 blocks: one launch for all of
+// them, or for the f32 products one for each kind.  One block is never taken as halves.
 template <int PREC>
 hipError_t launch_p(int rb, int kind, const XArgs &a, hipStream_t st) {
     if (kind == kDiag) {
         switch (rb) {
-            case 1: return launch_one<PREC, 1, kDiag>(a, st);
+            case 1:
+                if constexpr (PREC != kFP32H) return launch_one<PREC, 1, kDiag>(a, st);
+                break;
             case 2: return launch_one<PREC, 2, kDiag>(a, st);
             case 3: return launch_one<PREC, 3, kDiag>(a, st);
             case 4: return launch_one<PREC, 4, kDiag>(a, st);
             case 5: return launch_one<PREC, 5, kDiag>(a, st);
             case 6: return launch_one<PREC, 6, kDiag>(a, st);
         }
-    } else if (kind == kOffDiag) {
-        switch (rb) {
-            case 2: return launch_one<PREC, 2, kOffDiag>(a, st);
-            case 3: return launch_one<PREC, 3, kOffDiag>(a, st);
-            case 4: return launch_one<PREC, 4, kOffDiag>(a, st);
-        }
-    } else if (kind == kBoth) {
-        switch (rb) {
-            case 2: return launch_one<PREC, 2, kBoth>(a, st);
-            case 3: return launch_one<PREC, 3, kBoth>(a, st);
-            case 4: return launch_one<PREC, 4, kBoth>(a, st);
-        }
+    } else if (rb == 4 && kind == (PREC == kFP32 ? kOffDiag : kBoth)) {
+        return launch_one<PREC, 4, PREC == kFP32 ? kOffDiag : kBoth>(a, st);
     }
     return hipErrorInvalidValue;
 }

@@ -164,8 +164,7 @@ __device__ __forceinline__ uint4 half_of(uint4 v) {
 // rounding of the whole sum at every product added.  So a diagonal block's Re
 // keeps its small products apart: accR sums hi hi^T alone and acc3 hi lo^T, and
 // Re = accR + acc3 + acc3^T at the end (one product less, too).
-// SERIAL keeps one column's operands at a time in registers.
-template <int RB, bool DIAG, int RBJ, bool SERIAL, typename Row, typename Col>
+template <int RB, bool DIAG, int RBJ, typename Row, typename Col>
 __device__ __forceinline__ void add_halves(Row &&row, Col &&col, f32x4 (&accR)[RB][RBJ], f32x4 (&accI)[RB][RBJ],
                                            f32x4 (&acc3)[RB][RBJ]) {
     Halves p[RB];
@@ -193,7 +192,6 @@ __device__ __forceinline__ void add_halves(Row &&row, Col &&col, f32x4 (&accR)[R
             mma<kFP32H>(accR[I][J], p[I].h, b.h);
             mma<kFP32H>(accI[I][J], p[I].h, ch);
         }
-        if constexpr (SERIAL) __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -270,8 +268,8 @@ struct XRegion {
         };
         auto compute = [&](const uint4 (&pr)[RB][KB], const uint4 (&pc)[RBJ][KB]) {
             if constexpr (KB == 2) {
-                add_halves<RB, DIAG, RBJ, false>([&](int I) { return split_records(pr[I][0], pr[I][1], m1); },
-                                          [&](int J) { return split_records(pc[J][0], pc[J][1], m1); }, accR, accI, acc3);
+                add_halves<RB, DIAG, RBJ>([&](int I) { return split_records(pr[I][0], pr[I][1], m1); },
+                                     [&](int J) { return split_records(pc[J][0], pc[J][1], m1); }, accR, accI, acc3);
             } else {
                 uint4 r1[RB], c1[RBJ];
 #pragma unroll
@@ -806,11 +804,11 @@ __device__ __forceinline__ void x_chan_halves(const XArgs &a, int unit, uint4 *r
         if (st0 < st1)
             xh_loop<true>(a.spec, a.K, a.a_pad, f, st0, st1, wave, m1, raw0, raw1, hv0, hv1, [&](const uint4 *hv) {
                 auto drow = [&](int I) { return block(hv, rD + I); };
-                add_halves<4, true, 4, false>(drow, drow, D.accR, D.accI, D.acc3);
+                add_halves<4, true, 4>(drow, drow, D.accR, D.accI, D.acc3);
                 // one region's operands at a time
                 __builtin_amdgcn_sched_barrier(0);
-                add_halves<4, false, 2, false>([&](int I) { return block(hv, h.x + I); },
-                                               [&](int J) { return block(hv, h.y + J); }, H.accR, H.accI, H.acc3);
+                add_halves<4, false, 2>([&](int I) { return block(hv, h.x + I); },
+                                        [&](int J) { return block(hv, h.y + J); }, H.accR, H.accI, H.acc3);
             });
         D.store(a.partial, obase, a.N, rD, rD, tb + wave * 16 * 17);
         H.store(a.partial, obase, a.N, h.x, h.y, nullptr);
@@ -820,8 +818,8 @@ __device__ __forceinline__ void x_chan_halves(const XArgs &a, int unit, uint4 *r
         X.zero();
         if (st0 < st1)
             xh_loop<false>(a.spec, a.K, a.a_pad, f, st0, st1, wave, m1, raw0, raw1, hv0, hv1, [&](const uint4 *hv) {
-                add_halves<4, false, 4, false>([&](int I) { return block(hv, o.x + I); },
-                                               [&](int J) { return block(hv, o.y + J); }, X.accR, X.accI, X.acc3);
+                add_halves<4, false, 4>([&](int I) { return block(hv, o.x + I); },
+                                        [&](int J) { return block(hv, o.y + J); }, X.accR, X.accI, X.acc3);
             });
         X.store(a.partial, obase, a.N, o.x, o.y, nullptr);
     }
