@@ -99,9 +99,10 @@ int corr_set_precision(corr_handle h, int mode);
  *   chunk_spectra: spectra per F->X chunk (multiple of 64).
  *   x_splits:      time splits of one chunk in the X-stage (partials per
  *                  channel per chunk; 1..64).
- *   f_group:       antennas per F-stage tile (1, 2, 4, 8 or 16; without effect on FP16,
- *                  INT8 and INT16 records of 256 and 512 channels, whose units are
- *                  of one size).
+ *   f_group:       antennas per F-stage tile (1, 2, 4, 8 or 16).  FP16, INT8 and
+ *                  INT16 records of 256 and 512 channels are made in units of one
+ *                  size: there a value is checked against the same limits and
+ *                  reported by corr_get_tiles, but has no effect.
  * Allowed only before the first process call, else CORR_ESTATE.  */
 typedef struct {
     int chunk_spectra;

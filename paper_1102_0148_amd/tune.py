@@ -57,18 +57,30 @@ def key(N: int, K: int, S: int, prec: str, batch=False, mode: Optional[str] = No
     return f"{ARCH}:N={N}:K={K}:S={S}:{prec}" + suffix
 
 
+def default_group(K: int, prec: str) -> int:
+    """Antennas that fill one round of transforms, the library's default group or half of it."""
+    return max(1, 256 // (K // 16) // record_times(prec))
+
+
+def groups(K: int, prec: str) -> List[int]:
+    """The F groups to time: those whose tile fits the LDS, but one where the group has no effect
+    (fp16, int8 and int16 records of 256 and 512 channels are made in units of one size)."""
+    if prec != "fp32" and K in (256, 512):
+        return [default_group(K, prec)]
+    return [g for g in (1, 2, 4, 8, 16) if f_lds_bytes(K, prec, g) <= LDS_LIMIT]
+
+
 def candidates(N: int, K: int, S: int, prec: str) -> List[dict]:
     """Every tile choice the tuner considers for a single job."""
     whole = (S + 63) // 64 * 64
     chunks = sorted({c for c in (whole, whole // 2, whole // 4, 16384, 8192) if 1024 <= c <= whole and c % 64 == 0}
                     | {whole})
-    groups = [g for g in (1, 2, 4, 8, 16) if f_lds_bytes(K, prec, g) <= LDS_LIMIT]
     out = []
     for chunk in chunks:
         for s in SPLITS:
             if PARTIAL_LIMIT[prec] and chunk / s > PARTIAL_LIMIT[prec]:
                 continue
-            for g in groups:
+            for g in groups(K, prec):
                 out.append({"chunk_spectra": chunk, "x_splits": s, "f_group": g})
     return out
 
@@ -149,7 +161,7 @@ def tune_single(N: int, K: int, S: int, prec: str, log=print,
                 incumbent: Optional[dict] = None) -> Tuple[dict, float, List[Tuple[dict, float]]]:
     """Stage 1 times every (chunk, splits) at the default F group; stage 2
     picks the group by the F-stage time alone (the only stage it changes),
-    timing the groups in turn at the best chunk; stage 3 times the four best
+    timing the groups in turn at the best chunk, where there are several; stage 3 times the four best
     (chunk, splits) pairs of stage 1 with that group, and the incumbent
     table entry, in turn and keeps the lowest median end-to-end time (ties
     as in `pick`): the stage timers leave out the gaps between launches,
@@ -159,10 +171,8 @@ def tune_single(N: int, K: int, S: int, prec: str, log=print,
     import synth
     x = synth.packed(synth.recipe_plain(N=N, two_k=2 * K, seed=11), 0, S, device="cuda").contiguous()
     cands = candidates(N, K, S, prec)
-    groups = sorted({c["f_group"] for c in cands})
-    fpr = 256 // (K // 16)
-    dg = max(1, fpr // record_times(prec))
-    base_group = dg if dg in groups else min(groups)
+    every = groups(K, prec)
+    base_group = default_group(K, prec) if default_group(K, prec) in every else min(every)
     results = []
     for t in [c for c in cands if c["f_group"] == base_group]:
         ms = _time_single(corr, torch, N, K, S, prec, t, x)["total"]
@@ -170,9 +180,11 @@ def tune_single(N: int, K: int, S: int, prec: str, log=print,
         log(f"  {prec} N={N} K={K} {t} {ms:.4f} ms")
     top = [t for t, _ in sorted(results, key=lambda r: r[1])[:4]]
     chunk, splits = top[0]["chunk_spectra"], top[0]["x_splits"]
-    by_f = _rounds(corr, torch, N, K, S, prec, x,
-                   [{"chunk_spectra": chunk, "x_splits": splits, "f_group": g} for g in groups], "f", log=log)
-    group = min(by_f, key=lambda r: r[1])[0]["f_group"]
+    group = base_group
+    if len(every) > 1:
+        by_f = _rounds(corr, torch, N, K, S, prec, x,
+                       [{"chunk_spectra": chunk, "x_splits": splits, "f_group": g} for g in every], "f", log=log)
+        group = min(by_f, key=lambda r: r[1])[0]["f_group"]
     # integrations are cheap next to building a correlator: ten per timing,
     # five rounds, against the drift of the clock between rounds
     final = _rounds(corr, torch, N, K, S, prec, x, final_candidates(top, group, incumbent), "e2e",
