@@ -185,9 +185,8 @@ typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
 typedef float f4_t __attribute__((ext_vector_type(4)));
 
 // The reduced-precision records at 256 and 512 points are transformed in registers
-// on the matrix cores (fstage_reg_dev.h).  The float32 records (bound by their HBM
-// writes) and the calibration power sums, whose f32 precision f16 halves do not
-// reach, keep the vector transform here.
+// on the matrix cores (fstage_reg_dev.h).  The float32 records, bound by their HBM
+// writes, and the calibration power sums keep the vector transform here.
 template <int M, int PREC> constexpr bool reg_fft() { return (M == 256 || M == 512) && PREC != kFP32; }
 
 __device__ __forceinline__ f4_t mfma_h(h8_t a, h8_t b, f4_t c) {

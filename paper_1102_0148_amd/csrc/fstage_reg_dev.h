@@ -147,9 +147,9 @@ __device__ __forceinline__ void row_transpose(uint32_t &r0, uint32_t &r1, uint32
     r3 = d[1];
 }
 
-// Even lane groups keep x and take the odd groups' y' = x; odd groups ... : after it x
-// holds, in even groups, x of the pair's even group and, in odd ones, y of it; y the
-// same of the pair's odd group.
+// Lane groups 2p and 2p + 1 swap: the odd group's x with the even group's y.  After it
+// the even group holds both groups' x (its own in x, the odd one's in y), and the odd
+// group both groups' y (the even one's in x, its own in y).
 __device__ __forceinline__ void pair_exchange(uint32_t &x, uint32_t &y) {
     const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
     x = r[0];

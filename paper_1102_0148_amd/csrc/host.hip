@@ -1365,11 +1365,12 @@ int batch_build_branches(corr_ctx *b) {
     std::vector<int> order(nj);
     for (int j = 0; j < nj; ++j) order[j] = j;
     std::sort(order.begin(), order.end(), [&](int x, int y) { return work[x] > work[y]; });
-    // fp32 jobs (X-stage bound by the MFMA rate, F-stage by HBM writes) slow
-    // one another down side by side: the 12-job fp32 batch took 4.45 ms on
-    // four branches and 4.34 ms on one.  The int8 batch took 2.30 ms on four
-    // and 2.97 ms on one.  So the fp32 jobs share one branch, and the other
-    // jobs are dealt round-robin over the remaining branches.
+    // fp32 jobs (F-stage and X-stage bound by HBM) slow one another down side by
+    // side: twelve fp32 jobs of 16384 spectra took 11.0 ms on four branches and
+    // 10.6 ms on one, six of them beside six int8 ones 8.9 ms dealt like these and
+    // 8.6 ms on a branch of their own.  An int8 batch took 2.30 ms on four and
+    // 2.97 ms on one.  So the fp32 jobs share one branch, and the other jobs are
+    // dealt round-robin over the remaining branches.
     int n_f32 = 0;
     for (corr_ctx *h : b->jobs) n_f32 += h->prec == kFP32;
     const int f32_br = n_f32 ? 1 : 0;

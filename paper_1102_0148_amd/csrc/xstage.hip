@@ -13,7 +13,9 @@ constexpr int kOffDiag = 0, kDiag = 1, kBoth = 2;
 // ordinary VGPRs (without the bound the compiler splits them across VGPRs and
 // AGPRs, and the larger regions fall to one wave per SIMD); the fp32
 // off-diagonal 4 x 4-block region and the fp32 6-block diagonal region need
-// more than 256 registers and keep the default.
+// more than 256 registers and keep the default, and so does the 5-block one as
+// halves (X-stage of N = 80, K = 256, 8192 spectra: f32 products 432 us, halves 358
+// so bounded and 338 with one wave per SIMD; N = 96 582 and 505).
 template <int PREC, int RB, int KIND>
 constexpr int x_min_blocks() {
     return ((PREC == kFP32 || PREC == kFP32H) && ((RB >= 4 && KIND != kDiag) || RB >= (PREC == kFP32 ? 6 : 5))) ? 1 : 2;

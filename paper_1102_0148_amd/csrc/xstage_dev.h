@@ -90,15 +90,19 @@ __device__ __forceinline__ f32x4 mf32(float a, float b, f32x4 acc) {
 
 // Float records as f16 halves.  x = hi + lo with hi = x rounded to f16 (ties to
 // even) and lo = x - hi, exact in the f32 arithmetic of the mixed-precision fma,
-// rounded to f16: |x - hi - lo| <= 2^-23 |x| (and 2^-25 below 2^-3).  A product
-// of two values is summed from hi hi, lo hi and hi lo, each exact in the f32
-// accumulator; the lo lo term dropped is below 2^-22 of the product, and of
-// random sign but in the autocorrelations, which it leaves 2^-25 short.  Three
+// rounded to f16: |x - hi - lo| <= 2^-23 |x| (and 2^-25 where |x| < 2^-2, whose lo
+// is subnormal).  A product of two values is summed from hi hi, lo hi and hi lo,
+// each exact in the f32 accumulator; lo lo, below 2^-22 of the product, is left out
+// but in the real parts of a block of antennas with itself.  Three
 // f16 products at 16 times the rate of the f32 matrix instructions, and the
 // four-product form, which has none of the three-product form's cancellation:
 // against float64 the sums are nearer than those of the f32 products (relative
 // 2-norm, f32 products and halves: N = 44, K = 256, 65536 spectra 1.65e-7 and
-// 1.0e-7; N = 256, K = 512, 2048 spectra 9.1e-7 and 4.3e-7).  X-stage times, same
+// 1.0e-7; N = 256, K = 512, 2048 spectra 9.1e-7 and 4.3e-7), also where the operands'
+// errors do not average out (the same tone in every spectrum: N = 44, K = 256, 8192
+// spectra 5.1e-6 and 1.6e-6; N = 256, K = 256, 512 spectra 2.6e-6 and 8.4e-7), but for
+// autocorrelations whose every f32 sum happens to be exact (an impulse of 7 in every
+// block, N = 44, K = 256, 8192 spectra: 6.7e-7 and 1.0e-6).  X-stage times, same
 // box: N = 44, 65536 spectra 1.29 -> 1.18 ms (6.4 GB of records at 5.4 TB/s: now
 // bound by reading them); N = 64, K = 512, 16384 spectra 1.07 -> 0.81 ms; N = 160,
 // K = 256, 8192 spectra 2.06 -> 1.50 ms.
@@ -162,8 +166,8 @@ __device__ __forceinline__ uint4 half_of(uint4 v) {
 //
 // The autocorrelations' sums grow steadily and carry most of the error, a
 // rounding of the whole sum at every product added.  So a diagonal block's Re
-// keeps its small products apart: accR sums hi hi^T alone and acc3 hi lo^T, and
-// Re = accR + acc3 + acc3^T at the end (one product less, too).
+// keeps its small products apart: accR sums hi hi^T alone and acc3 hi lo^T +
+// lo lo^T / 2, and Re = accR + acc3 + acc3^T at the end.
 template <int RB, bool DIAG, int RBJ, typename Row, typename Col>
 __device__ __forceinline__ void add_halves(Row &&row, Col &&col, f32x4 (&accR)[RB][RBJ], f32x4 (&accI)[RB][RBJ],
                                            f32x4 (&acc3)[RB][RBJ]) {
@@ -269,7 +273,7 @@ struct XRegion {
         auto compute = [&](const uint4 (&pr)[RB][KB], const uint4 (&pc)[RBJ][KB]) {
             if constexpr (KB == 2) {
                 add_halves<RB, DIAG, RBJ>([&](int I) { return split_records(pr[I][0], pr[I][1], m1); },
-                                     [&](int J) { return split_records(pc[J][0], pc[J][1], m1); }, accR, accI, acc3);
+                                          [&](int J) { return split_records(pc[J][0], pc[J][1], m1); }, accR, accI, acc3);
             } else {
                 uint4 r1[RB], c1[RBJ];
 #pragma unroll

@@ -30,7 +30,8 @@ ARCH = "gfx950"
 LDS_LIMIT = 160 * 1024
 SPLITS = (1, 2, 4, 8, 12, 16, 24, 32, 48, 64)
 # spectra one partial may sum, per form: fp32 partials stay short for
-# accuracy (its three-product form cancels), fp16's error is its spectra's up
+# accuracy (the f32 products' three-product form cancels, and a coherent
+# signal's roundings add up in any), fp16's error is its spectra's up
 # to 16384; int16 digit sums must stay exact in int32; int8 sums always are
 PARTIAL_LIMIT = {"fp32": 2048, "fp16": 16384, "int16": 16384, "int8": None}
 
