@@ -67,6 +67,15 @@ __global__ __launch_bounds__(kThreads, 2) void fstage_reg_kernel(FArgs kargs) {
     const int t8 = (sets + 7) / 8;
     const int x = blockIdx.x % 8, rank = blockIdx.x / 8, wgs = gridDim.x / 8;
     const int lo = x * t8, hi = min(lo + t8, sets);
+    unsigned *const ctr = args.ticket + kTicketStride * x;
+    if constexpr (TRACK && M == 512) {
+        // (short of registers: what follows spills more here, N = 44, 4096 spectra int8
+        // 231 -> 242 us)
+        reg_load_ops<M>(args, lds);
+        __syncthreads();
+        reg_units_dyn<M, PREC, TRACK>(args, lo, hi, ctr, s_tk, lds);
+        return;
+    }
     // A workgroup's first two sets go by its rank on the XCD, so that their tickets,
     // the samples and the operands are not fetched one after another.  Calls queued
     // back to back, before and so (us; with the LDS transform of up to 16 sequences a
@@ -82,7 +91,7 @@ __global__ __launch_bounds__(kThreads, 2) void fstage_reg_kernel(FArgs kargs) {
     reg_load_set<M, PREC>(args, set, raw);
     reg_load_ops<M>(args, lds);  // waits for the samples too
     __syncthreads();
-    reg_sets<M, PREC, TRACK>(args, set, set + wgs, lo + 2 * wgs, hi, args.ticket + kTicketStride * x, s_tk, lds, raw);
+    reg_sets<M, PREC, TRACK>(args, set, set + wgs, lo + 2 * wgs, hi, ctr, s_tk, lds, raw);
 }
 
 template <int M, int PREC, bool TRACK>
