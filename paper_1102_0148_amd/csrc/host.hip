@@ -442,15 +442,16 @@ int plan_fused(corr_ctx *h) {
     if (h->K > arg_waves)
         return fail(CORR_EINVAL, "the fused pipeline needs %d X waves for K=%d, has %d", h->K, h->K, arg_waves);
     const int arg_nsplit = std::max(1, std::min(64, arg_waves / h->K));
-    // fp32: the products as halves, but in partials of a few spectra, and where three workgroups share a CU and two or three
-    // antenna blocks leave the halves' kernel short of registers: there only in
-    // the layouts that X bounds.  S = 16384, f32 products and halves (us), N = 44,
-    // K = 128 with two F workgroups a CU 380 and 427, one 468 and 393, 24 CUs an
-    // XCD on F 667 and 411; N = 32, K = 128 with 8 and 16 such CUs 417 and 436, 291
-    // and 303, with 20 316 and 266; N = 48, K = 256, 736 and 773, 891 and 735, 1267
-    // and 760.  Two workgroups a CU (N = 44, K = 512) 1634 and 1274; one block (N = 12,
+    // fp32: the products as halves, but in partials of a few spectra, and where
+    // three workgroups share a CU and two or three antenna blocks leave the halves'
+    // kernel short of registers: there only in the layouts that X bounds.  S = 16384,
+    // f32 products and halves (us), N = 44, K = 128 with two F workgroups a CU 380 and
+    // 427, one 468 and 393, 24 CUs an XCD on F 667 and 411; N = 32, K = 128 with 8 and
+    // 16 such CUs 417 and 436, 291 and 303, with 20 316 and 266; N = 48, K = 256, 736
+    // and 773, 891 and 735, 1267 and 760; N = 44, K = 256, 4096 spectra with 16 CUs 239
+    // and 227.  Two workgroups a CU (N = 44, K = 512) 1634 and 1274; one block (N = 12,
     // K = 256) 302 and 294.
-    const bool x_bound = fcus ? 16 * fcus > cus : fpc == 1;
+    const bool x_bound = !fcus ? fpc == 1 : h->rb == 3 ? 16 * fcus >= cus : 16 * fcus > cus;
     const int nkb = round_up((h->S + h->TG - 1) / h->TG, step_records(h->prec)) / 4;
     const bool halves = h->prec == kFP32 && enough_for_halves(nkb, arg_nsplit) && (per_cu < 3 || h->rb == 1 || x_bound);
     h->fx_xprec = halves ? kFP32H : h->prec;
