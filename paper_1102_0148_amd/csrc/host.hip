@@ -428,7 +428,12 @@ int plan_fused(corr_ctx *h) {
     h->fx_cus = cus;
     // The register transform's kernels keep two workgroups per CU (72 KB of
     // operands and 256 registers), the other forms' three or more.  Their
-    // layout arguments are taken as for three and cut to what two can run.
+    // layout arguments are taken as for three and cut to what two can run.  That
+    // costs layouts that leave few X waves to one or two blocks of antennas (fp16,
+    // 16384 spectra, before the register transform and now: N = 8, K = 256, one F
+    // workgroup a CU 135 and 160 us, 24 CUs an XCD on F 188 and 212; N = 16 193 and
+    // 233); the default and every other layout gained (171 and 160; 204 and 184;
+    // N = 44 1434 and 1300 for 65536 spectra).
     const int arg_per_cu = uses_reg_fft(h->K, h->prec) ? std::max(per_cu, 3) : per_cu;
     int fcus = h->fx_fcus, fpc = h->fx_fpc ? h->fx_fpc : arg_per_cu - 1;
     if (fcus >= cus / 8)
