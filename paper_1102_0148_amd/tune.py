@@ -64,11 +64,16 @@ def default_group(K: int, prec: str) -> int:
 
 
 def groups(K: int, prec: str) -> List[int]:
-    """The F groups to time: those whose tile fits the LDS, but one where the group has no effect
-    (fp16, int8 and int16 records of 256 and 512 channels are made in units of one size)."""
+    """The F groups that the library takes: those whose tile fits the LDS."""
+    return [g for g in (1, 2, 4, 8, 16) if f_lds_bytes(K, prec, g) <= LDS_LIMIT]
+
+
+def groups_to_time(K: int, prec: str) -> List[int]:
+    """The F groups that differ: all of them, but one where the group has no effect (fp16, int8 and
+    int16 records of 256 and 512 channels are made in units of one size)."""
     if prec != "fp32" and K in (256, 512):
         return [default_group(K, prec)]
-    return [g for g in (1, 2, 4, 8, 16) if f_lds_bytes(K, prec, g) <= LDS_LIMIT]
+    return groups(K, prec)
 
 
 def candidates(N: int, K: int, S: int, prec: str) -> List[dict]:
@@ -172,7 +177,7 @@ def tune_single(N: int, K: int, S: int, prec: str, log=print,
     import synth
     x = synth.packed(synth.recipe_plain(N=N, two_k=2 * K, seed=11), 0, S, device="cuda").contiguous()
     cands = candidates(N, K, S, prec)
-    every = groups(K, prec)
+    every = groups_to_time(K, prec)
     base_group = default_group(K, prec) if default_group(K, prec) in every else min(every)
     results = []
     for t in [c for c in cands if c["f_group"] == base_group]:

@@ -9,5 +9,6 @@ from paper_1102_0148_amd import tune
                                            (512, "int8", [1]), (512, "int16", [2]), (256, "fp32", [1, 2, 4, 8, 16]),
                                            (1024, "fp16", [1, 2, 4]), (128, "int8", [1, 2, 4, 8, 16])])
 def test_groups(K, prec, expect):
-    assert tune.groups(K, prec) == expect
-    assert sorted({c["f_group"] for c in tune.candidates(44, K, 4096, prec)}) == expect
+    assert tune.groups_to_time(K, prec) == expect
+    # the library takes others too
+    assert set(expect) <= {c["f_group"] for c in tune.candidates(44, K, 4096, prec)} == set(tune.groups(K, prec))
