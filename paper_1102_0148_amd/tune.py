@@ -77,7 +77,7 @@ def groups_to_time(K: int, prec: str) -> List[int]:
 
 
 def candidates(N: int, K: int, S: int, prec: str) -> List[dict]:
-    """Every tile choice the tuner considers for a single job."""
+    """Every choice of the tuner's chunks and splits and of the groups that the library takes."""
     whole = (S + 63) // 64 * 64
     chunks = sorted({c for c in (whole, whole // 2, whole // 4, 16384, 8192) if 1024 <= c <= whole and c % 64 == 0}
                     | {whole})
